@@ -5,10 +5,13 @@
 // tiles.  Operand tiles move global -> LDS with direct loads
 // (global_load_lds_dwordx4) into a double-buffered LDS tile.  LDS rows are 64
 // bf16 (128 B) with the eight 16-byte chunks XOR-swizzled (swz below) so
-// fragment loads are free of bank conflicts.  Two kernels:
+// fragment loads are free of bank conflicts.  Three kernels:
+//  - gemm_bf16_ring_kernel: four waves on 64 x 64, 128 x 64 or 128 x 128
+//    tiles, a ring of LDS stages, the fragments of a whole k-tile in registers
+//    (launches with few tiles, and 128 x 128 tiles two blocks per CU);
 //  - gemm_bf16_kernel: four waves in a 2 x 2 grid, one barrier per k-tile,
 //    the fragment reads of k step s + 1 scheduled between the MFMAs of step s
-//    (128 x 128 tiles, two blocks per CU; small and ragged shapes);
+//    (192 x 128 tiles, two blocks per CU);
 //  - gemm_bf16_w4_kernel: four waves, one per SIMD, on a 256 x 256 or
 //    256 x 128 tile, A double- and B triple-buffered in LDS (every GEMM of
 //    the 8B-shaped pass); gemm_bf16_w4_split_kernel runs both tile shapes
@@ -215,6 +218,7 @@ struct StagedEpi {
   static constexpr int bytes =
       (EPI == EPI_STORE_F32 || EPI == EPI_RESIDUAL) ? BM * PF * 4
       : EPI == EPI_GELU                              ? BM * PB * 2
+      : BN < 128                                     ? BM * PF * 4  // paired, staged as fp32
       : EPI == EPI_SWIGLU                            ? BM * PS * 2
       : (BM * PB > BN * PV ? BM * PB : BN * PV) * 2;
   static constexpr int main_bytes = MAIN;
@@ -249,6 +253,30 @@ __device__ __forceinline__ void epilogue_staged(f32x16 (&acc)[WM / 32][WN / 32],
         xres[it] = *reinterpret_cast<const float4*>((const float*)ea.out + (size_t)grow * ea.ldo + gcol);
     }
   }
+  // Pairs of 32-column blocks (rotary lo / hi, SwiGLU gate / up) split between
+  // two waves: the fp32 accumulators are staged, and phase 2 pairs them, eight
+  // pairs per thread and chunk (V has no pairs).  The rotary table entries
+  // are loaded first, like the residual rows.
+  constexpr bool SPLIT_PAIRS = (EPI == EPI_QKV_ROPE || EPI == EPI_SWIGLU) && TN % 2 != 0;
+  constexpr int CPRP = BN / 16, ITP = SPLIT_PAIRS ? BM * CPRP / NT : 1;
+  static_assert(!SPLIT_PAIRS || BM * CPRP % NT == 0, "pair chunks must split evenly over the threads");
+  f32x4 rot[EPI == EPI_QKV_ROPE && SPLIT_PAIRS ? ITP : 1][4];
+  if constexpr (EPI == EPI_QKV_ROPE && SPLIT_PAIRS) {
+    const int half = ea.dh / 2;
+    if (n0 / ea.d < 2)
+#pragma unroll
+      for (int it = 0; it < ITP; ++it) {
+        const int qi = tid + it * NT, row = qi / CPRP, c8 = qi % CPRP;
+        const int t = min(m0 + row, Mv - 1) % ea.T;
+        const int dlo = ((n0 + (c8 >> 2) * 64) % ea.d % ea.dh) / 64 * 32 + (c8 & 3) * 8;
+        const f32x4* cp = reinterpret_cast<const f32x4*>(ea.rope_cos + t * half + dlo);
+        const f32x4* sp = reinterpret_cast<const f32x4*>(ea.rope_sin + t * half + dlo);
+        rot[it][0] = cp[0];
+        rot[it][1] = cp[1];
+        rot[it][2] = sp[0];
+        rot[it][3] = sp[1];
+      }
+  }
   // the main loop's last barrier ends every read of the operand tiles
   if constexpr (EPI == EPI_STORE_F32 || EPI == EPI_RESIDUAL || EPI == EPI_GELU) {
 #pragma unroll
@@ -263,7 +291,17 @@ __device__ __forceinline__ void epilogue_staged(f32x16 (&acc)[WM / 32][WN / 32],
           else
             sf[row * SE::PF + col] = acc[i][j][r];
         }
-  } else if constexpr (EPI == EPI_SWIGLU) {
+  } else if (SPLIT_PAIRS && (EPI == EPI_SWIGLU || n0 / ea.d < 2)) {
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+      for (int j = 0; j < TN; ++j)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+          const int row = wr0 + i * 32 + (r >> 2) * 8 + lg * 4 + (r & 3), col = wc0 + j * 32 + lr;
+          sf[row * SE::PF + col] = acc[i][j][r];
+        }
+  } else if constexpr (EPI == EPI_SWIGLU && !SPLIT_PAIRS) {
 #pragma unroll
     for (int j = 0; j < TN; j += 2)
 #pragma unroll
@@ -274,10 +312,11 @@ __device__ __forceinline__ void epilogue_staged(f32x16 (&acc)[WM / 32][WN / 32],
           const int f = (wc0 + j * 32) / 2 + lr;
           smem[row * SE::PS + f] = f32_to_bf16(silu(acc[i][j][r]) * acc[i][j + 1][r]);
         }
-  } else {  // EPI_QKV_ROPE: the block tile lies inside one of Q, K, V (d % BN == 0)
+  } else if constexpr (EPI == EPI_QKV_ROPE) {  // the tile lies inside one of Q, K, V (d % BN == 0)
     const int d = ea.d, dh = ea.dh, T = ea.T, half = dh / 2;
     const int which = n0 / d;
     if (which < 2) {
+      if constexpr (!SPLIT_PAIRS) {
       constexpr int NP = TN / 2;  // (lo, hi) pairs of 32-column blocks per wave tile row
       int hb[NP], dlo[NP];        // local column of the head's first dim; dim of lo
 #pragma unroll
@@ -315,6 +354,7 @@ __device__ __forceinline__ void epilogue_staged(f32x16 (&acc)[WM / 32][WN / 32],
             smem[row * SE::PB + hb[p] + dlo[p] + half] = f32_to_bf16(rot_hi(lo, hi, c, s));
           }
       }
+      }
     } else {
       // V, dim-major: 4 consecutive rows of one column are one 8-byte write
 #pragma unroll
@@ -334,7 +374,44 @@ __device__ __forceinline__ void epilogue_staged(f32x16 (&acc)[WM / 32][WN / 32],
   __syncthreads();
   // phase 2: 16-byte chunks, a fixed number per thread (EPI_STORE_F32 with
   // no output: the row statistics only)
-  if constexpr (EPI == EPI_STORE_F32 || EPI == EPI_RESIDUAL) {
+  if (SPLIT_PAIRS && (EPI == EPI_SWIGLU || n0 / ea.d < 2)) {
+    auto pack = [](const float(&v)[8]) {
+      u32x4 w;
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        w[e] = (uint32_t)f32_to_bf16(v[2 * e]) | ((uint32_t)f32_to_bf16(v[2 * e + 1]) << 16);
+      return w;
+    };
+#pragma unroll
+    for (int it = 0; it < ITP; ++it) {
+      const int qi = tid + it * NT, row = qi / CPRP, c8 = qi % CPRP, c = (c8 & 3) * 8;
+      const int grow = m0 + row, col = (c8 >> 2) * 64 + c;  // col: lo / gate, + 32: hi / up
+      if (grow >= Mv) continue;
+      const f32x4* src = reinterpret_cast<const f32x4*>(sf + row * SE::PF + col);
+      const f32x4 a[2] = {src[0], src[1]}, b[2] = {src[8], src[9]};
+      float lo[8], hi[8];
+      if constexpr (EPI == EPI_SWIGLU) {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) lo[e] = silu(a[e / 4][e % 4]) * b[e / 4][e % 4];
+        bf16_t* dst = (bf16_t*)ea.out + (size_t)grow * ea.ldo + (n0 + (c8 >> 2) * 64) / 2 + c;
+        *reinterpret_cast<u32x4*>(dst) = pack(lo);
+      } else if constexpr (EPI == EPI_QKV_ROPE) {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+          const float x = a[e / 4][e % 4], y = b[e / 4][e % 4];
+          const float cc = rot[it][e / 4][e % 4], ss = rot[it][2 + e / 4][e % 4];
+          lo[e] = rot_lo(x, y, cc, ss);
+          hi[e] = rot_hi(x, y, cc, ss);
+        }
+        const int which = n0 / ea.d, within = n0 - which * ea.d + (c8 >> 2) * 64;
+        const int h = within / ea.dh, dlo = within % ea.dh / 64 * 32 + c;
+        const int b_ = grow / ea.T, t = grow - b_ * ea.T;
+        bf16_t* dst = (bf16_t*)(which == 0 ? ea.q : ea.k) + (((size_t)b_ * ea.H + h) * ea.Tp + t) * ea.dh + dlo;
+        *reinterpret_cast<u32x4*>(dst) = pack(lo);
+        *reinterpret_cast<u32x4*>(dst + ea.dh / 2) = pack(hi);
+      }
+    }
+  } else if constexpr (EPI == EPI_STORE_F32 || EPI == EPI_RESIDUAL) {
 #pragma unroll
     for (int it = 0; it < IT4; ++it) {
       if (EPI == EPI_STORE_F32 && !ea.out) break;
@@ -899,6 +976,190 @@ gemm_bf16_w4_split_kernel(const bf16_t* __restrict__ A, const bf16_t* __restrict
                             (int)blockIdx.x - nb1, smem);
 }
 
+// ---------------------------------------------------------------------------
+// Ring kernel: BM x BN tiles (64 or 128 rows and columns) with the operands in
+// a ring of NS LDS stages, loaded NS k-tiles ahead, for launches whose tiles
+// do not fill the chip.  There a CU has one or two blocks, so nothing hides
+// the latency of a load but the loads issued before it; with two stages and a
+// full wait per k-tile a k-tile took a round trip to memory (0.8 us on
+// 128 x 128 tiles at 48 tiles in the launch).  Four waves in a WR x 4/WR grid;
+// each wave holds all the MFMA fragments of a k-tile in registers and reads
+// those of the next one under its MFMAs.
+//
+// What bounds it then is the LDS: per k-tile a CU reads the fragments and
+// writes the loads, 48 KB (64 x 64), 72 KB (128 x 64) or 96 KB (128 x 128), and
+// every shape takes 11 cycles per KB of that (0.22, 0.33, 0.46 us per k-tile).
+// So a launch takes the largest tile that still gives every CU one, and tiles
+// that share a CU share its LDS: the time goes by tiles per CU.
+//
+// Measured at 1024 rows of the small model (K = 768; FFN-out K = 3072), with
+// the kernels it replaces there: QKV 20.2 -> 10.6 us, O-proj 14.1 -> 5.8, FFN-in
+// (GELU) 16.4 -> 11.7, FFN-out 38.3 -> 12.5.  At 777 rows of the 8B shape:
+// O-proj 52 -> 35 us, FFN-out 131 -> 88.  128 x 128 tiles with two stages, two
+// blocks per CU, 65536 rows: O-proj (K = 768) 148 -> 138 us against the kernel
+// that read one k step ahead.
+//
+// Interval kt: wait until this wave's loads of tile kt + 1 have landed and its
+// fragment reads of tile kt are done; barrier (so every wave's loads have
+// landed and stage kt % NS is free); issue the loads of tile kt + NS into that
+// stage; read the fragments of tile kt + 1; MFMAs of tile kt.
+//
+// Numerics: the k steps of each k-tile in order, as in the other kernels.
+template <int BM, int BN, int NS, int WR, int EPI>
+__global__ void __launch_bounds__(256)
+gemm_bf16_ring_kernel(const bf16_t* __restrict__ A, const bf16_t* __restrict__ Bw, int M, int N,
+                      int K, const int* __restrict__ M_dev, EpiArgs ea, int n_tm, int n_tn) {
+  constexpr int WM = BM / WR, WN = BN / (4 / WR);
+  constexpr int TM = WM / 32, TN = WN / 32;
+  constexpr int A_IN = BM / 32, B_IN = BN / 32;  // 1 KB direct loads per wave per k-tile
+  constexpr int NL = A_IN + B_IN, KS = BK / 16;
+  static_assert(TM >= 1 && TN >= 1 && NS >= 2 && (NS - 1) * NL < 64, "wave tile / vmcnt field");
+  using SE = StagedEpi<BM, BN, EPI, NS * (BM + BN) * BK * 2, 0>;
+  static_assert(SE::enabled, "staged epilogue");
+  __shared__ __attribute__((aligned(16))) bf16_t smem[SE::smem_elems];
+
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wm = wave / (4 / WR), wn = wave % (4 / WR);
+  const int lr = lane & 31, lg = lane >> 5;
+  const int Mv = M_dev ? min(*M_dev, M) : M;
+  int tm, tn;
+  if (!tile_coords(blockIdx.x, n_tm, n_tn, BM, Mv, tm, tn)) return;
+  const int m0 = tm * BM, n0 = tn * BN;
+  const int nk = K / BK;
+
+  bf16_t* As = smem;
+  bf16_t* Bs = smem + NS * BM * BK;
+  // window j of a wave: 8 tile rows, lane l fetching chunk (l & 7) ^ swz(row)
+  // of row l / 8; rows past the live rows or columns are clamped
+  // (byte offsets from a base that advances with k: below 2^32, so that a load
+  // takes a scalar base and one 32-bit register)
+  uint32_t a_off[A_IN], b_off[B_IN];
+#pragma unroll
+  for (int j = 0; j < A_IN; ++j) {
+    const int row = (wave * A_IN + j) * 8 + (lane >> 3);
+    a_off[j] = 2u * (uint32_t)(min(m0 + row, Mv - 1) * K + (((lane & 7) ^ swz(row)) << 3));
+  }
+#pragma unroll
+  for (int j = 0; j < B_IN; ++j) {
+    const int row = (wave * B_IN + j) * 8 + (lane >> 3);
+    b_off[j] = 2u * (uint32_t)(min(n0 + row, N - 1) * K + (((lane & 7) ^ swz(row)) << 3));
+  }
+  const int a_win = wave * A_IN * 512, b_win = wave * B_IN * 512;
+  // load i of the NL loads of tile kt
+  auto load_one = [&](int kt, int stage, int i) {
+    if (i < A_IN)
+      lds_dma16((const bf16_t*)((const char*)(A + kt * BK) + a_off[i]), As + stage * BM * BK + a_win + i * 512);
+    else
+      lds_dma16((const bf16_t*)((const char*)(Bw + kt * BK) + b_off[i - A_IN]),
+                Bs + stage * BN * BK + b_win + (i - A_IN) * 512);
+  };
+
+  f32x16 acc[TM][TN];
+#pragma unroll
+  for (int i = 0; i < TM; ++i)
+#pragma unroll
+    for (int j = 0; j < TN; ++j)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.0f;
+
+  bf16x8 fa[2][KS][TM], fb[2][KS][TN];
+  // fragment reads of k step s of a tile
+  auto read_step = [&](int stage, auto set_, int s) {
+    constexpr int S = decltype(set_)::value;
+    load_frags<TN>(fb[S][s], Bs + stage * BN * BK, wn * WN, lr, 2 * s + lg);
+    load_frags<TM>(fa[S][s], As + stage * BM * BK, wm * WM, lr, 2 * s + lg);
+  };
+
+#pragma unroll
+  for (int t = 0; t < NS; ++t)
+    if (t < nk)
+#pragma unroll
+      for (int i = 0; i < NL; ++i) load_one(t, t, i);
+  if (nk >= NS)
+    __builtin_amdgcn_s_waitcnt(waitcnt_vm((NS - 1) * NL));
+  else
+    __builtin_amdgcn_s_waitcnt(waitcnt_vm(0));
+  block_barrier();
+#pragma unroll
+  for (int s = 0; s < KS; ++s) read_step(0, std::integral_constant<int, 0>{}, s);
+
+  int st0 = 0, st1 = 1;  // stages of tiles kt and kt + 1
+  // FULL: tiles kt + 1 .. kt + NS exist
+  auto trip = [&](int kt, auto set_, auto full_) {
+    constexpr int S = decltype(set_)::value;
+    constexpr bool FULL = decltype(full_)::value;
+    // loads younger than tile kt + 1's: of tiles kt + 2 .. min(nk, kt + NS) - 1
+    if constexpr (FULL) {
+      __builtin_amdgcn_s_waitcnt(waitcnt_vm((NS - 2) * NL));
+    } else {
+      const int younger = nk - 2 - kt;
+      if (younger >= NS - 2) __builtin_amdgcn_s_waitcnt(waitcnt_vm((NS - 2) * NL));
+      static_for<1, NS - 2>([&](auto y_) {
+        constexpr int Y = decltype(y_)::value;
+        if (younger == Y) __builtin_amdgcn_s_waitcnt(waitcnt_vm(Y * NL));
+      });
+      if (younger <= 0) __builtin_amdgcn_s_waitcnt(waitcnt_vm(0));
+    }
+    // ties the fragments of tile kt to this point: the compiler's own wait for
+    // their reads is placed here, not after the reads of the next tile
+#pragma unroll
+    for (int s = 0; s < KS; ++s) {
+#pragma unroll
+      for (int i = 0; i < TM; ++i) asm volatile("" : "+v"(fa[S][s][i]));
+#pragma unroll
+      for (int j = 0; j < TN; ++j) asm volatile("" : "+v"(fb[S][s][j]));
+    }
+    block_barrier();
+    if constexpr (FULL) {
+      // a k step's MFMAs, then its share of the fragment reads and loads, which
+      // issue while the MFMAs run
+      static_for<0, KS>([&](auto s_) {
+        constexpr int s = decltype(s_)::value;
+        mfma_block<TM, TN>(acc, fa[S][s], fb[S][s]);
+        read_step(st1, std::integral_constant<int, S ^ 1>{}, s);
+        static_for<s * NL / KS, (s + 1) * NL / KS>([&](auto i_) { load_one(kt + NS, st0, decltype(i_)::value); });
+        __builtin_amdgcn_sched_barrier(0);
+      });
+    } else {
+      if (kt + NS < nk)
+#pragma unroll
+        for (int i = 0; i < NL; ++i) load_one(kt + NS, st0, i);
+      if (kt + 1 < nk)
+#pragma unroll
+        for (int s = 0; s < KS; ++s) read_step(st1, std::integral_constant<int, S ^ 1>{}, s);
+#pragma unroll
+      for (int s = 0; s < KS; ++s) mfma_block<TM, TN>(acc, fa[S][s], fb[S][s]);
+    }
+    st0 = st1;
+    st1 = st1 + 1 == NS ? 0 : st1 + 1;
+  };
+  using Set0 = std::integral_constant<int, 0>;
+  using Set1 = std::integral_constant<int, 1>;
+  int kt = 0;
+  for (; kt + 1 + NS < nk; kt += 2) {
+    trip(kt, Set0{}, std::true_type{});
+    trip(kt + 1, Set1{}, std::true_type{});
+  }
+  for (; kt + 1 < nk; kt += 2) {
+    trip(kt, Set0{}, std::false_type{});
+    trip(kt + 1, Set1{}, std::false_type{});
+  }
+  if (kt < nk) trip(kt, Set0{}, std::false_type{});
+  // the last interval's barrier followed every wave's last fragment read, so
+  // the stages are free for the epilogue
+  epilogue_staged<BM, BN, EPI, WM, WN, 256>(acc, smem, m0, n0, wm, wn, tid, Mv, N, ea);
+}
+
+template <int BM, int BN, int NS, int WR, int EPI>
+void launch_ring(hipStream_t st, const bf16_t* A, const bf16_t* B, int M, int N, int K,
+                 const int* M_dev, const EpiArgs& ea) {
+  const int n_tm = ceil_div(M, BM), n_tn = ceil_div(N, BN);
+  gemm_bf16_ring_kernel<BM, BN, NS, WR, EPI><<<dim3(round_up(n_tm * n_tn, 8)), dim3(256), 0, st>>>(
+      A, B, M, N, K, M_dev, ea, n_tm, n_tn);
+  DLMC_HIP(hipGetLastError());
+}
+
 // columns [c0, c1) of C, both multiples of BN
 template <int EPI, int BN>
 void launch_w4(hipStream_t st, const bf16_t* A, const bf16_t* B, int M, int N, int K,
@@ -954,23 +1215,34 @@ void launch_256(hipStream_t st, const bf16_t* A, const bf16_t* B, int M, int N, 
   }
 }
 
-template <int BM, int BN>
-void launch(hipStream_t st, const bf16_t* A, const bf16_t* B, int M, int N, int K,
-            const int* M_dev, EpiKind epi, const EpiArgs& ea) {
+// 192 x 128 tiles
+void launch_192(hipStream_t st, const bf16_t* A, const bf16_t* B, int M, int N, int K,
+                const int* M_dev, EpiKind epi, const EpiArgs& ea) {
   switch (epi) {
-    case EPI_STORE_F32: launch_epi<BM, BN, EPI_STORE_F32>(st, A, B, M, N, K, M_dev, ea); break;
-    case EPI_RESIDUAL: launch_epi<BM, BN, EPI_RESIDUAL>(st, A, B, M, N, K, M_dev, ea); break;
-    case EPI_GELU: launch_epi<BM, BN, EPI_GELU>(st, A, B, M, N, K, M_dev, ea); break;
-    case EPI_QKV_ROPE:
-    case EPI_SWIGLU:
-      if constexpr (BN == 256) {
-        throw Error(DLMC_E_INVAL, "paired epilogues use BN = 128");
-      } else if (epi == EPI_QKV_ROPE) {
-        launch_epi<BM, BN, EPI_QKV_ROPE>(st, A, B, M, N, K, M_dev, ea);
-      } else {
-        launch_epi<BM, BN, EPI_SWIGLU>(st, A, B, M, N, K, M_dev, ea);
-      }
+    case EPI_STORE_F32: launch_epi<192, 128, EPI_STORE_F32>(st, A, B, M, N, K, M_dev, ea); break;
+    case EPI_RESIDUAL: launch_epi<192, 128, EPI_RESIDUAL>(st, A, B, M, N, K, M_dev, ea); break;
+    case EPI_GELU: launch_epi<192, 128, EPI_GELU>(st, A, B, M, N, K, M_dev, ea); break;
+    case EPI_QKV_ROPE: launch_epi<192, 128, EPI_QKV_ROPE>(st, A, B, M, N, K, M_dev, ea); break;
+    case EPI_SWIGLU: launch_epi<192, 128, EPI_SWIGLU>(st, A, B, M, N, K, M_dev, ea); break;
+  }
+}
+
+// ring kernel of one tile shape and stage count (the fp32 store's row
+// statistics need whole 128-column groups)
+template <int BM, int BN, int NS>
+void launch_ring_epi(hipStream_t st, const bf16_t* A, const bf16_t* B, int M, int N, int K,
+                     const int* M_dev, EpiKind epi, const EpiArgs& ea) {
+  switch (epi) {
+    case EPI_STORE_F32:
+      if constexpr (BN % STAT_GROUP == 0)
+        launch_ring<BM, BN, NS, 2, EPI_STORE_F32>(st, A, B, M, N, K, M_dev, ea);
+      else
+        throw Error(DLMC_E_INVAL, "fp32 store tiles are 128 columns wide");
       break;
+    case EPI_RESIDUAL: launch_ring<BM, BN, NS, 2, EPI_RESIDUAL>(st, A, B, M, N, K, M_dev, ea); break;
+    case EPI_GELU: launch_ring<BM, BN, NS, 2, EPI_GELU>(st, A, B, M, N, K, M_dev, ea); break;
+    case EPI_QKV_ROPE: launch_ring<BM, BN, NS, 2, EPI_QKV_ROPE>(st, A, B, M, N, K, M_dev, ea); break;
+    case EPI_SWIGLU: launch_ring<BM, BN, NS, 2, EPI_SWIGLU>(st, A, B, M, N, K, M_dev, ea); break;
   }
 }
 
@@ -995,9 +1267,9 @@ GemmTiles gemm_bf16_tiles(int M, int N, int K, EpiKind epi, int d, int rows_hint
   const int ei = (int)epi;
   //                    fp32 store  residual  QKV   GELU  SwiGLU
   static const double c0_128[5] = {9.3, 9.6, 5.9, 5.0, 5.0};
-  static const double c0_w128[5] = {10.6, 13.0, 8.5, 11.7, 11.7};
+  static const double c0_w128[5] = {10.6, 13.0, 8.5, 11.7, 3.0};
   static const double c0_w256[5] = {21.5, 50.7, 18.3, 25.9, 7.0};
-  static const double c0_192[5] = {17.9, 20.5, 9.0, 9.7, 5.0};
+  static const double c0_192[5] = {17.9, 20.5, 9.0, 9.7, 20.0};
   const double nk = (double)K / BK;
   // c0s: the fixed cost of a wave of tiles that follows another, where it
   // differs from the first wave's
@@ -1014,7 +1286,7 @@ GemmTiles gemm_bf16_tiles(int M, int N, int K, EpiKind epi, int d, int rows_hint
   // 12288, M = 65536).
   const double c0s_w128 =
       epi == EPI_RESIDUAL ? c0_w128[ei] * std::min(1.0, std::sqrt(768.0 / (double)K)) : -1.0;
-  const double t128 = t_of(128, 128, 512, c0_128[ei], 1.26, N);
+  const double t128 = t_of(128, 128, 512, c0_128[ei], 1.13, N);
   // 192 x 128: QKV tiles must lie inside Q, K or V (d % 128 == 0 holds)
   const double t192 = t_of(192, 128, 512, c0_192[ei], 1.253, N);
   double t4 = 1e300;
@@ -1023,7 +1295,10 @@ GemmTiles gemm_bf16_tiles(int M, int N, int K, EpiKind epi, int d, int rows_hint
   const bool wide_ok = epi != EPI_QKV_ROPE || d % 256 == 0;
   if (N % 128 == 0) {
     auto t_split = [&](int c1) {
-      return t_of(256, 256, 256, c0_w256[ei], 1.53, c1) + t_of(256, 128, 256, c0_w128[ei], 0.98, N - c1, c0s_w128);
+      // with few 256 x 128 tiles a k-tile takes less than with every CU busy
+      const double busy = std::min(1.0, ceil_div(live, 256) * (double)((N - c1) / 128) / 256.0);
+      return t_of(256, 256, 256, c0_w256[ei], 1.53, c1) +
+             t_of(256, 128, 256, c0_w128[ei], 0.62 + 0.36 * busy * busy, N - c1, c0s_w128);
     };
     // one tile shape (all 256 x 128, or all 256 x 256), then a split if it
     // is more than 3% faster (the estimate rounds each part up to whole
@@ -1042,9 +1317,48 @@ GemmTiles gemm_bf16_tiles(int M, int N, int K, EpiKind epi, int d, int rows_hint
       }
     }
   }
-  if (t192 < t128 && (split < 0 || t192 < t4)) return {GEMM_TILES_192x128, 0};
-  if (split >= 0 && t4 <= t128) return {GEMM_TILES_4WAVE, split};
-  return {GEMM_TILES_128x128, 0};
+  GemmTiles best = {GEMM_TILES_128x128, 0, 0};
+  double t_best = t128;
+  if (split >= 0 && t4 <= t_best) {
+    best = {GEMM_TILES_4WAVE, split, 0};
+    t_best = t4;
+  }
+  if (t192 < t_best) {
+    best = {GEMM_TILES_192x128, 0, 0};
+    t_best = t192;
+  }
+  // The ring kernel: tiles that share a CU share its LDS, which bounds them, so
+  // its time goes by the tiles per CU (256 CUs), not by waves of slots; fitted to
+  // 64 .. 16384 rows of the small model and 64 .. 3072 of the 8B shape (within
+  // 8% rms for the multi-block shapes, 15% for the one-block ones).  A launch
+  // of at most one tile per CU takes the deep ring (with less LDS per block the
+  // others run two or three blocks per CU: 15.0 against 12.5 us for 192 tiles
+  // of 64 x 64 at K = 3072, but 10.6 against 11.4 us for 576 at K = 768).
+  struct RingShape {
+    int kind, bm, bn, deep;
+    double c1, c0[5], c0s, c0s_res;  // c0s: each further tile of a CU (c0s_res: the residual update's)
+  };
+  //                                                          store resid QKV GELU SwiGLU
+  static const RingShape ring[] = {
+      {GEMM_TILES_64x64, 64, 64, 1, 0.243, {0.0, 2.0, 2.9, 3.2, 3.0}, 0.0, 0.0},
+      {GEMM_TILES_64x64, 64, 64, 0, 0.212, {0.0, 2.6, 2.5, 3.4, 16.3}, 0.23, 0.5},
+      {GEMM_TILES_128x64, 128, 64, 1, 0.365, {0.0, 2.0, 6.1, 3.0, 4.0}, 0.0, 0.0},
+      {GEMM_TILES_128x64, 128, 64, 0, 0.334, {0.0, 3.0, 3.1, 4.6, 8.7}, 0.91, 2.2},
+      {GEMM_TILES_128x128_DEEP, 128, 128, 1, 0.448, {8.0, 4.2, 7.3, 7.2, 20.8}, 0.0, 0.0},
+  };
+  for (const RingShape& r : ring) {
+    if (epi == EPI_STORE_F32 && r.bn < 128) continue;
+    const long tiles = (long)ceil_div(live, r.bm) * ceil_div(N, r.bn), per_cu = (tiles + 255) / 256;
+    // 128 x 64: six stages against three pay from about 32 k-tiles on
+    const bool deep = tiles <= 256 && (r.kind != GEMM_TILES_128x64 || K >= 2048);
+    if (deep != (r.deep != 0)) continue;
+    const double t = per_cu * nk * r.c1 + r.c0[ei] + (per_cu - 1) * (epi == EPI_RESIDUAL ? r.c0s_res : r.c0s);
+    if (t < t_best) {
+      best = {r.kind, 0, r.deep};
+      t_best = t;
+    }
+  }
+  return best;
 }
 
 void gemm_bf16(hipStream_t st, const bf16_t* A, const bf16_t* B, int M, int N, int K,
@@ -1059,17 +1373,30 @@ void gemm_bf16(hipStream_t st, const bf16_t* A, const bf16_t* B, int M, int N, i
   DLMC_CHECK(epi != EPI_QKV_ROPE || (ea.d % 128 == 0 && (ea.dh == 64 || ea.dh == 128)),
              DLMC_E_INVAL, "QKV epilogue needs d % 128 == 0 and head dim 64 or 128");
   const GemmTiles tc = gemm_bf16_tiles(M, N, K, epi, ea.d, rows_hint);
-  if (tc.kind == GEMM_TILES_192x128) {
-    launch<192, 128>(st, A, B, M, N, K, M_dev, epi, ea);
-  } else if (tc.kind == GEMM_TILES_4WAVE) {
-    if (tc.split > 0 && tc.split < N) {
-      launch_split(st, A, B, M, N, K, M_dev, epi, ea, tc.split);
-    } else {
-      launch_256<256>(st, A, B, M, N, K, M_dev, epi, ea, 0, tc.split);
-      launch_256<128>(st, A, B, M, N, K, M_dev, epi, ea, tc.split, N);
-    }
-  } else {
-    launch<128, 128>(st, A, B, M, N, K, M_dev, epi, ea);
+  switch (tc.kind) {
+    case GEMM_TILES_192x128: launch_192(st, A, B, M, N, K, M_dev, epi, ea); break;
+    case GEMM_TILES_4WAVE:
+      if (tc.split > 0 && tc.split < N) {
+        launch_split(st, A, B, M, N, K, M_dev, epi, ea, tc.split);
+      } else {
+        launch_256<256>(st, A, B, M, N, K, M_dev, epi, ea, 0, tc.split);
+        launch_256<128>(st, A, B, M, N, K, M_dev, epi, ea, tc.split, N);
+      }
+      break;
+    case GEMM_TILES_64x64:
+      if (tc.deep)
+        launch_ring_epi<64, 64, 4>(st, A, B, M, N, K, M_dev, epi, ea);
+      else
+        launch_ring_epi<64, 64, 3>(st, A, B, M, N, K, M_dev, epi, ea);
+      break;
+    case GEMM_TILES_128x64:
+      if (tc.deep)
+        launch_ring_epi<128, 64, 6>(st, A, B, M, N, K, M_dev, epi, ea);
+      else
+        launch_ring_epi<128, 64, 3>(st, A, B, M, N, K, M_dev, epi, ea);
+      break;
+    case GEMM_TILES_128x128_DEEP: launch_ring_epi<128, 128, 4>(st, A, B, M, N, K, M_dev, epi, ea); break;
+    default: launch_ring_epi<128, 128, 2>(st, A, B, M, N, K, M_dev, epi, ea); break;
   }
 }
 

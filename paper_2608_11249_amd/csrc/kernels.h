@@ -32,11 +32,20 @@ struct EpiArgs {
 };
 
 // Tile shape of a bf16 GEMM (the choice never changes the result):
-// 128 x 128 or 192 x 128 tiles two blocks per CU, or the 4-wave kernel with
-// columns [0, split) on 256 x 256 tiles and [split, N) on 256 x 128 tiles.
-enum GemmTileKind { GEMM_TILES_128x128 = 0, GEMM_TILES_192x128 = 1, GEMM_TILES_4WAVE = 2 };
+// 128 x 128 or 192 x 128 tiles two blocks per CU; the 4-wave kernel with
+// columns [0, split) on 256 x 256 tiles and [split, N) on 256 x 128 tiles; or,
+// for launches with few tiles, the ring kernel on 64 x 64, 128 x 64 or
+// (one block per CU) 128 x 128 tiles.  deep: more LDS stages, fewer blocks per CU.
+enum GemmTileKind {
+  GEMM_TILES_128x128 = 0,
+  GEMM_TILES_192x128 = 1,
+  GEMM_TILES_4WAVE = 2,
+  GEMM_TILES_64x64 = 3,
+  GEMM_TILES_128x64 = 4,
+  GEMM_TILES_128x128_DEEP = 5
+};
 struct GemmTiles {
-  int kind, split;
+  int kind, split, deep;
 };
 // the choice gemm_bf16 makes for these sizes (d: the QKV epilogue's model
 // width); host only
