@@ -325,57 +325,120 @@ attn_bf16_kernel(const bf16_t* __restrict__ Q, const bf16_t* __restrict__ Kg,
   }
 }
 
-// fp32 path: one thread per query, 64-key tiles staged in LDS, exact-order
-// online softmax with expf.  Used by the fp32 model only (small shapes).
+// fp32 path: the same scheme on v_mfma_f32_16x16x4_f32.  A wave owns 16
+// queries and computes S^T = K Q^T (16 keys x 16 queries per tile), so a lane
+// holds 4 scores of one query per tile: keys 4 g + r of lane group g = lane /
+// 16, register r.  The PV product takes register r of every lane as one k
+// step (keys 4 g + r, g = 0 .. 3), so P^T needs no shuffle and a lane's V^T
+// operands of the four steps are 4 consecutive keys, one 16-byte LDS read; K
+// and Q use the same trick over dims (step s of a 16-dim group: dims 4 g + s).
+// Rows of the LDS tiles carry 4 floats of padding, which puts the 16 rows a
+// 16-lane read touches on distinct banks.  64-key tiles in a fixed order with
+// expf and an online softmax; statistics are per lane and merged over the four
+// lane groups at the end (row sums) or per tile (row max).
+//
+// Bound by the latency of short chunks (256 keys: four tiles) and, for more,
+// by the MFMAs.  The kernel it replaces gave a thread a whole query, 256 waves
+// at 16 chunks x 4 heads x 256 queries of dim 32, each reading every K and V
+// element from LDS by itself: 196 us there, against 15.5 us.
 template <int DH>
-__global__ void __launch_bounds__(64)
+__global__ void __launch_bounds__(256)
 attn_f32_kernel(const float* __restrict__ Q, const float* __restrict__ Kg,
                 const float* __restrict__ Vt, float* __restrict__ O, int H, int T, int Tp,
                 float scale) {
-  __shared__ float Ks[64][DH + 1];
-  __shared__ float Vs[64][DH + 1];
-  const int tid = threadIdx.x, h = blockIdx.y, b = blockIdx.z;
+  constexpr int KP = DH + 4, VP = KT + 4, ND = DH / 16;
+  __shared__ __attribute__((aligned(16))) float Ks[KT * KP];
+  __shared__ __attribute__((aligned(16))) float Vs[DH * VP];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, lr = lane & 15, lg = lane >> 4;
+  const int h = blockIdx.y, b = blockIdx.z;
   const size_t bh = (size_t)b * H + h;
-  const int q = blockIdx.x * 64 + tid;
-  float qv[DH], o[DH];
+  const int q = blockIdx.x * 64 + wave * 16 + lr;
+  const float* Kp = Kg + bh * Tp * DH;
+  const float* Vp = Vt + bh * DH * Tp;
+  f32x4 qf[ND], o[ND];
 #pragma unroll
-  for (int d = 0; d < DH; ++d) {
-    qv[d] = Q[(bh * Tp + min(q, T - 1)) * DH + d];
-    o[d] = 0.0f;
+  for (int t = 0; t < ND; ++t) {
+    qf[t] = *reinterpret_cast<const f32x4*>(Q + (bh * Tp + min(q, T - 1)) * DH + 16 * t + 4 * lg);
+    o[t] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
   }
   float m = -INFINITY, l = 0.0f;
-  for (int k0 = 0; k0 < T; k0 += 64) {
-    const int nk = min(64, T - k0);
-    for (int i = tid; i < 64 * DH; i += 64) {
-      const int kk = i / DH, d = i % DH;
-      const int key = min(k0 + kk, T - 1);
-      Ks[kk][d] = Kg[(bh * Tp + key) * DH + d];
-      Vs[kk][d] = Vt[(bh * DH + d) * Tp + key];
+  for (int k0 = 0; k0 < T; k0 += KT) {
+    // Tp is a multiple of 128: every row read is inside the buffers, and rows
+    // at or beyond T hold finite values and get zero probability
+    __syncthreads();
+    for (int i = tid; i < KT * DH / 4; i += 256) {
+      const int r = i / (DH / 4), c = i % (DH / 4) * 4;
+      *reinterpret_cast<f32x4*>(Ks + r * KP + c) = *reinterpret_cast<const f32x4*>(Kp + (size_t)(k0 + r) * DH + c);
+    }
+    for (int i = tid; i < DH * KT / 4; i += 256) {
+      const int r = i / (KT / 4), c = i % (KT / 4) * 4;
+      *reinterpret_cast<f32x4*>(Vs + r * VP + c) = *reinterpret_cast<const f32x4*>(Vp + (size_t)r * Tp + k0 + c);
     }
     __syncthreads();
-    for (int kk = 0; kk < nk; ++kk) {
-      float s = 0.0f;
+    f32x4 s[KT / 16];
 #pragma unroll
-      for (int d = 0; d < DH; ++d) s += qv[d] * Ks[kk][d];
-      s *= scale;
-      if (s > m) {
-        const float corr = expf(m - s);
-        l *= corr;
+    for (int kt = 0; kt < KT / 16; ++kt) s[kt] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
-        for (int d = 0; d < DH; ++d) o[d] *= corr;
-        m = s;
+    for (int t = 0; t < ND; ++t) {
+      f32x4 kf[KT / 16];
+#pragma unroll
+      for (int kt = 0; kt < KT / 16; ++kt)
+        kf[kt] = *reinterpret_cast<const f32x4*>(Ks + (kt * 16 + lr) * KP + 16 * t + 4 * lg);
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+#pragma unroll
+        for (int kt = 0; kt < KT / 16; ++kt)
+          s[kt] = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[kt][e], qf[t][e], s[kt], 0, 0, 0);
+    }
+    float mx = -INFINITY;
+#pragma unroll
+    for (int kt = 0; kt < KT / 16; ++kt)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        s[kt][r] = k0 + kt * 16 + lg * 4 + r < T ? s[kt][r] * scale : -INFINITY;
+        mx = fmaxf(mx, s[kt][r]);
       }
-      const float p = expf(s - m);
-      l += p;
+    mx = fmaxf(mx, __shfl_xor(mx, 16));
+    mx = fmaxf(mx, __shfl_xor(mx, 32));
+    const float m_new = fmaxf(m, mx);
+    const float alpha = expf(m - m_new);
+    m = m_new;
+    l *= alpha;
 #pragma unroll
-      for (int d = 0; d < DH; ++d) o[d] += p * Vs[kk][d];
+    for (int t = 0; t < ND; ++t)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) o[t][r] *= alpha;
+#pragma unroll
+    for (int kt = 0; kt < KT / 16; ++kt)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        s[kt][r] = expf(s[kt][r] - m);
+        l += s[kt][r];
+      }
+#pragma unroll
+    for (int kt = 0; kt < KT / 16; ++kt) {
+      f32x4 vf[ND];
+#pragma unroll
+      for (int t = 0; t < ND; ++t)
+        vf[t] = *reinterpret_cast<const f32x4*>(Vs + (16 * t + lr) * VP + kt * 16 + 4 * lg);
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+#pragma unroll
+        for (int t = 0; t < ND; ++t)
+          o[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(vf[t][r], s[kt][r], o[t], 0, 0, 0);
     }
-    __syncthreads();
   }
+  l += __shfl_xor(l, 16);
+  l += __shfl_xor(l, 32);
   if (q < T) {
     float* orow = O + ((size_t)b * T + q) * (size_t)(H * DH) + h * DH;
 #pragma unroll
-    for (int d = 0; d < DH; ++d) orow[d] = o[d] / l;
+    for (int t = 0; t < ND; ++t) {
+      f32x4 v;
+#pragma unroll
+      for (int r = 0; r < 4; ++r) v[r] = o[t][r] / l;
+      *reinterpret_cast<f32x4*>(orow + 16 * t + 4 * lg) = v;
+    }
   }
 }
 
@@ -412,7 +475,8 @@ void attention_bf16(hipStream_t st, const bf16_t* q, const bf16_t* k, const bf16
 void attention_f32(hipStream_t st, const float* q, const float* k, const float* vt, float* out,
                    int B, int H, int T, int Tp, int dh) {
   if (B <= 0 || T <= 0) return;
-  dim3 grid(ceil_div(T, 64), H, B), block(64);
+  DLMC_CHECK(Tp % 128 == 0 && Tp >= T, DLMC_E_INVAL, "attention: padded length must be a multiple of 128");
+  dim3 grid(ceil_div(T, 64), H, B), block(256);
   const float scale = 1.0f / sqrtf((float)dh);
   switch (dh) {
     case 16: attn_f32_kernel<16><<<grid, block, 0, st>>>(q, k, vt, out, H, T, Tp, scale); break;

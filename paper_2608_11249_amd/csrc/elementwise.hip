@@ -181,59 +181,132 @@ __global__ void fill_kernel(int32_t* p, int32_t v, size_t n) {
 }
 
 // ---------------------------------------------------------------- fp32 model
-// 64 x 64 tile, 16-deep k steps through LDS, 4 x 4 outputs per thread;
-// every output is a sequential fmaf chain over k.
+// 32 x 64 tiles on v_mfma_f32_16x16x4_f32, four waves in a 2 x 2 grid of 16 x 32
+// sub-tiles, 64-deep k stages through LDS with the next stage's global loads in
+// registers.  An MFMA takes k indices {4 g + s : g = 0 .. 3} of a 16-deep group
+// as its step s, so a lane (g = lane / 16) reads its operands of four steps as
+// one 16-byte chunk; every output is the sum in one fixed order of k, whatever
+// the launch, and columns of zeros past K add nothing.  LDS rows carry 4 floats
+// of padding: the 16 rows a 16-lane read touches start on distinct banks.
+//
+// The fp32 model's launches are short (4096 rows, K = 128 or 512, N = 128 ..
+// 512), so small tiles that fill the CUs matter more than reuse: O-proj and
+// FFN-out take 8.8 us on average, 24.2 with 64 x 64 tiles on the vector units,
+// QKV with its rotary step 11.1 (13.4 + 6.8) and FFN-in with GELU 12.1
+// (13.4 + 6.2): EPI_QKV_ROPE and EPI_GELU save a pass over the output each.
+constexpr int GF_BM = 32, GF_BN = 64, GF_BK = 64, GF_P = GF_BK + 4;
+
 template <int EPI>
 __global__ void __launch_bounds__(256)
 gemm_f32_kernel(const float* __restrict__ A, const float* __restrict__ Bw, int M, int N, int K,
                 const int* __restrict__ M_dev, EpiArgs ea) {
-  __shared__ float As[16][64 + 4];
-  __shared__ float Bs[16][64 + 4];
+  __shared__ __attribute__((aligned(16))) float sm[(GF_BM + GF_BN) * GF_P];
+  float* As = sm;
+  float* Bs = sm + GF_BM * GF_P;
   const int Mv = M_dev ? min(*M_dev, M) : M;
-  const int m0 = blockIdx.y * 64, n0 = blockIdx.x * 64;
+  const int m0 = blockIdx.y * GF_BM, n0 = blockIdx.x * GF_BN;
   if (m0 >= Mv) return;
-  const int tid = threadIdx.x, tx = tid & 15, ty = tid >> 4;
-  const int lrow = tid >> 2, lk = (tid & 3) * 4;
-  const float* ap = A + (size_t)min(m0 + lrow, Mv - 1) * K + lk;
-  const float* bp = Bw + (size_t)min(n0 + lrow, N - 1) * K + lk;
-  float acc[4][4] = {};
-  for (int k0 = 0; k0 < K; k0 += 16) {
-    const f32x4 a = *reinterpret_cast<const f32x4*>(ap + k0);
-    const f32x4 b = *reinterpret_cast<const f32x4*>(bp + k0);
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int wm = wave >> 1, wn = wave & 1, lr = lane & 15, lg = lane >> 4;
+  // staging: thread t moves chunk t % 16 of rows t / 16, + 16, ...
+  constexpr int CPR = GF_BK / 4, RPP = 256 / CPR, NA = GF_BM / RPP, NB = GF_BN / RPP;
+  const int sr = tid / CPR, sc = tid % CPR * 4;
+  const float* ap[NA];
+  const float* bp[NB];
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      As[lk + e][lrow] = a[e];
-      Bs[lk + e][lrow] = b[e];
-    }
+  for (int i = 0; i < NA; ++i) ap[i] = A + (size_t)min(m0 + sr + i * RPP, Mv - 1) * K;
+#pragma unroll
+  for (int i = 0; i < NB; ++i) bp[i] = Bw + (size_t)min(n0 + sr + i * RPP, N - 1) * K;
+  f32x4 ra[NA], rb[NB];
+  auto load = [&](int k0) {
+    const bool in = k0 + sc < K;  // K % 16 == 0: a chunk is inside K or past it
+#pragma unroll
+    for (int i = 0; i < NA; ++i)
+      ra[i] = in ? *reinterpret_cast<const f32x4*>(ap[i] + k0 + sc) : f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+    for (int i = 0; i < NB; ++i)
+      rb[i] = in ? *reinterpret_cast<const f32x4*>(bp[i] + k0 + sc) : f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+  };
+  f32x4 acc[2] = {f32x4{0.0f, 0.0f, 0.0f, 0.0f}, f32x4{0.0f, 0.0f, 0.0f, 0.0f}};
+  load(0);
+  for (int k0 = 0; k0 < K; k0 += GF_BK) {
     __syncthreads();
 #pragma unroll
-    for (int kk = 0; kk < 16; ++kk) {
-      float av[4], bv[4];
+    for (int i = 0; i < NA; ++i) *reinterpret_cast<f32x4*>(As + (sr + i * RPP) * GF_P + sc) = ra[i];
+#pragma unroll
+    for (int i = 0; i < NB; ++i) *reinterpret_cast<f32x4*>(Bs + (sr + i * RPP) * GF_P + sc) = rb[i];
+    __syncthreads();
+    if (k0 + GF_BK < K) load(k0 + GF_BK);
+#pragma unroll
+    for (int t = 0; t < GF_BK / 16; ++t) {
+      const f32x4 a = *reinterpret_cast<const f32x4*>(As + (wm * 16 + lr) * GF_P + 16 * t + 4 * lg);
+      const f32x4 b0 = *reinterpret_cast<const f32x4*>(Bs + (wn * 32 + lr) * GF_P + 16 * t + 4 * lg);
+      const f32x4 b1 = *reinterpret_cast<const f32x4*>(Bs + (wn * 32 + 16 + lr) * GF_P + 16 * t + 4 * lg);
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
-        av[e] = As[kk][ty * 4 + e];
-        bv[e] = Bs[kk][tx * 4 + e];
+        acc[0] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[e], b0[e], acc[0], 0, 0, 0);
+        acc[1] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[e], b1[e], acc[1], 0, 0, 0);
       }
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) acc[i][j] = fmaf(av[i], bv[j], acc[i][j]);
     }
-    __syncthreads();
   }
+  // acc[j][r] holds row 4 lg + r, column 16 j + lr of the wave's sub-tile
+  if constexpr (EPI == EPI_QKV_ROPE) {
+    // canonical columns; the tile lies inside one of Q, K, V and holds whole
+    // heads (d % 64 == 0, dh <= 64 a divisor of 64): rotary pairs from LDS
+    constexpr int P = GF_BN + 4;
+    __syncthreads();
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const int row = m0 + ty * 4 + i;
-    if (row >= Mv) continue;
+    for (int j = 0; j < 2; ++j)
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int col = n0 + tx * 4 + j;
+      for (int r = 0; r < 4; ++r) sm[(wm * 16 + 4 * lg + r) * P + wn * 32 + 16 * j + lr] = acc[j][r];
+    __syncthreads();
+    const int d = ea.d, dh = ea.dh, half = dh / 2, which = n0 / d;
+    if (which < 2) {
+      const int row = tid >> 3, p4 = (tid & 7) * 4, hh = p4 / half, p = p4 % half;  // 4 pairs
+      const int grow = m0 + row;
+      if (grow >= Mv) return;
+      const int b = grow / ea.T, t = grow - b * ea.T, h = (n0 - which * d) / dh + hh;
+      const f32x4 lo = *reinterpret_cast<const f32x4*>(sm + row * P + hh * dh + p);
+      const f32x4 hi = *reinterpret_cast<const f32x4*>(sm + row * P + hh * dh + p + half);
+      const f32x4 c = *reinterpret_cast<const f32x4*>(ea.rope_cos + t * half + p);
+      const f32x4 s = *reinterpret_cast<const f32x4*>(ea.rope_sin + t * half + p);
+      float* dst = (float*)(which == 0 ? ea.q : ea.k) + (((size_t)b * ea.H + h) * ea.Tp + t) * dh + p;
+      f32x4 x, y;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        x[e] = lo[e] * c[e] - hi[e] * s[e];
+        y[e] = hi[e] * c[e] + lo[e] * s[e];
+      }
+      *reinterpret_cast<f32x4*>(dst) = x;
+      *reinterpret_cast<f32x4*>(dst + half) = y;
+    } else {
+      // V transposed: 8 rows (positions) of one column
+      const int col = tid & 63, r0 = (tid >> 6) * 8, v = n0 - 2 * d + col;
+      for (int e = 0; e < 8; ++e) {
+        const int grow = m0 + r0 + e;
+        if (grow >= Mv) break;
+        const int b = grow / ea.T, t = grow - b * ea.T;
+        ((float*)ea.vt)[(((size_t)b * ea.H + v / dh) * dh + v % dh) * ea.Tp + t] = sm[(r0 + e) * P + col];
+      }
+    }
+  } else {
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      const int col = n0 + wn * 32 + 16 * j + lr;
       if (col >= N) continue;
-      float* o = (float*)ea.out + (size_t)row * ea.ldo + col;
-      if constexpr (EPI == EPI_RESIDUAL)
-        *o += acc[i][j];
-      else
-        *o = acc[i][j];
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int row = m0 + wm * 16 + 4 * lg + r;
+        if (row >= Mv) continue;
+        float* o = (float*)ea.out + (size_t)row * ea.ldo + col;
+        const float v = acc[j][r];
+        if constexpr (EPI == EPI_RESIDUAL)
+          *o += v;
+        else if constexpr (EPI == EPI_GELU)
+          *o = 0.5f * v * (1.0f + erff(v * 0.70710678118654752440f));
+        else
+          *o = v;
+      }
     }
   }
 }
@@ -263,19 +336,14 @@ __global__ void qkv_rope_f32_kernel(const float* __restrict__ qkv, int M, EpiArg
   }
 }
 
-__global__ void ffn_act_f32_kernel(const float* __restrict__ in, float* __restrict__ out, int M,
-                                   int F, int kind) {
+// SwiGLU over gate and up columns F apart (GELU is fused into its GEMM)
+__global__ void swiglu_f32_kernel(const float* __restrict__ in, float* __restrict__ out, int M, int F) {
   const size_t n = (size_t)M * F;
   for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
        i += (size_t)gridDim.x * blockDim.x) {
     const int row = (int)(i / F), f = (int)(i % F);
-    if (kind == DLMC_FFN_GELU) {
-      const float v = in[i];
-      out[i] = 0.5f * v * (1.0f + erff(v * 0.70710678118654752440f));
-    } else {
-      const float g = in[(size_t)row * 2 * F + f], u = in[(size_t)row * 2 * F + F + f];
-      out[i] = g / (1.0f + expf(-g)) * u;
-    }
+    const float g = in[(size_t)row * 2 * F + f], u = in[(size_t)row * 2 * F + F + f];
+    out[i] = g / (1.0f + expf(-g)) * u;
   }
 }
 
@@ -458,15 +526,22 @@ void gemm_f32(hipStream_t st, const float* A, const float* B, int M, int N, int 
               const int* M_dev, EpiKind epi, const EpiArgs& ea) {
   DLMC_CHECK(K % 16 == 0 && K > 0, DLMC_E_INVAL, "fp32 GEMM needs K % 16 == 0");
   if (M <= 0 || N <= 0) return;
-  dim3 grid(ceil_div(N, 64), ceil_div(M, 64)), block(256);
-  if (epi == EPI_RESIDUAL)
-    gemm_f32_kernel<EPI_RESIDUAL><<<grid, block, 0, st>>>(A, B, M, N, K, M_dev, ea);
-  else if (epi == EPI_STORE_F32)
-    gemm_f32_kernel<EPI_STORE_F32><<<grid, block, 0, st>>>(A, B, M, N, K, M_dev, ea);
-  else
-    throw Error(DLMC_E_INVAL, "fp32 GEMM epilogue must be store or residual");
+  dim3 grid(ceil_div(N, GF_BN), ceil_div(M, GF_BM)), block(256);
+  switch (epi) {
+    case EPI_RESIDUAL: gemm_f32_kernel<EPI_RESIDUAL><<<grid, block, 0, st>>>(A, B, M, N, K, M_dev, ea); break;
+    case EPI_STORE_F32: gemm_f32_kernel<EPI_STORE_F32><<<grid, block, 0, st>>>(A, B, M, N, K, M_dev, ea); break;
+    case EPI_GELU: gemm_f32_kernel<EPI_GELU><<<grid, block, 0, st>>>(A, B, M, N, K, M_dev, ea); break;
+    case EPI_QKV_ROPE:
+      DLMC_CHECK(gemm_f32_fuses_rope(ea.d, ea.dh) && N == 3 * ea.d, DLMC_E_INVAL,
+                 "fp32 QKV epilogue needs d % 64 == 0 and a head dim that divides 64");
+      gemm_f32_kernel<EPI_QKV_ROPE><<<grid, block, 0, st>>>(A, B, M, N, K, M_dev, ea);
+      break;
+    default: throw Error(DLMC_E_INVAL, "fp32 GEMM has no such epilogue");
+  }
   DLMC_HIP(hipGetLastError());
 }
+
+bool gemm_f32_fuses_rope(int d, int dh) { return d % GF_BN == 0 && GF_BN % dh == 0; }
 
 void qkv_rope_f32(hipStream_t st, const float* qkv, int M, const EpiArgs& ea) {
   const size_t n = (size_t)M * ea.H * (ea.dh / 2);
@@ -475,10 +550,10 @@ void qkv_rope_f32(hipStream_t st, const float* qkv, int M, const EpiArgs& ea) {
   DLMC_HIP(hipGetLastError());
 }
 
-void ffn_act_f32(hipStream_t st, const float* in, float* out, int M, int F, int kind) {
+void swiglu_f32(hipStream_t st, const float* in, float* out, int M, int F) {
   const size_t n = (size_t)M * F;
   if (n == 0) return;
-  ffn_act_f32_kernel<<<grid_for(n, 256), 256, 0, st>>>(in, out, M, F, kind);
+  swiglu_f32_kernel<<<grid_for(n, 256), 256, 0, st>>>(in, out, M, F);
   DLMC_HIP(hipGetLastError());
 }
 

@@ -58,9 +58,13 @@ void gemm_bf16(hipStream_t st, const bf16_t* A, const bf16_t* B, int M, int N, i
 void gemm_f32(hipStream_t st, const float* A, const float* B, int M, int N, int K,
               const int* M_dev, EpiKind epi, const EpiArgs& ea);
 
-// fp32 path helpers (the bf16 path fuses these into GEMM epilogues)
+// whether gemm_f32 takes EPI_QKV_ROPE at this width and head dim
+bool gemm_f32_fuses_rope(int d, int dh);
+
+// fp32 path helpers (fused into GEMM epilogues elsewhere): rotary for widths
+// gemm_f32 does not fuse, and SwiGLU
 void qkv_rope_f32(hipStream_t st, const float* qkv, int M, const EpiArgs& ea);
-void ffn_act_f32(hipStream_t st, const float* in, float* out, int M, int F, int kind);
+void swiglu_f32(hipStream_t st, const float* in, float* out, int M, int F);
 
 // ---------------------------------------------------------------- attention
 // Non-causal softmax(Q K^T / sqrt(dh)) V over all T keys of each chunk.

@@ -378,8 +378,12 @@ void dlmc_model::forward(const int32_t* st_dev, int B, int T, float* logits_out,
       t3.ldo = 3 * d;
       {
         StageTimer t(this, DLMC_STAGE_QKV, 2.0 * Md * 3.0 * dd * dd);
-        gemm_f32(s, (const float*)h, (const float*)w.wqkv, M, 3 * d, d, nullptr, EPI_STORE_F32, t3);
-        qkv_rope_f32(s, tmp, M, qkv);
+        if (gemm_f32_fuses_rope(d, dh)) {
+          gemm_f32(s, (const float*)h, (const float*)w.wqkv, M, 3 * d, d, nullptr, EPI_QKV_ROPE, qkv);
+        } else {
+          gemm_f32(s, (const float*)h, (const float*)w.wqkv, M, 3 * d, d, nullptr, EPI_STORE_F32, t3);
+          qkv_rope_f32(s, tmp, M, qkv);
+        }
       }
       if (attn_maps) attention_map(layer_index);
       {
@@ -410,12 +414,12 @@ void dlmc_model::forward(const int32_t* st_dev, int B, int T, float* logits_out,
       }
     } else {
       EpiArgs t2;
-      t2.out = tmp;
+      t2.out = glu ? tmp : (float*)ffn;
       t2.ldo = nF;
       {
         StageTimer t(this, DLMC_STAGE_FFN_IN, 2.0 * Md * nF * dd);
-        gemm_f32(s, (const float*)h, (const float*)w.win, M, nF, d, nullptr, EPI_STORE_F32, t2);
-        ffn_act_f32(s, tmp, (float*)ffn, M, F, cfg.ffn_kind);
+        gemm_f32(s, (const float*)h, (const float*)w.win, M, nF, d, nullptr, glu ? EPI_STORE_F32 : EPI_GELU, t2);
+        if (glu) swiglu_f32(s, tmp, (float*)ffn, M, F);
       }
       {
         StageTimer t(this, DLMC_STAGE_FFN_OUT, 2.0 * Md * dd * F);
