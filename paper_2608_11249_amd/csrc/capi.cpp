@@ -40,27 +40,6 @@ void use(dlmc_model* m) {
   DLMC_HIP(hipSetDevice(m->device));
 }
 
-// Device buffers of one call, freed when it returns or throws.
-struct DevBufs {
-  std::vector<void*> held;
-  template <typename T>
-  T* alloc(size_t bytes) {
-    void* q = nullptr;
-    if (hipMalloc(&q, std::max<size_t>(bytes, 16)) != hipSuccess || !q) {
-      (void)hipGetLastError();
-      throw Error(DLMC_E_NOMEM, "hipMalloc of " + std::to_string(bytes) + " bytes failed");
-    }
-    held.push_back(q);
-    return (T*)q;
-  }
-  DevBufs() = default;
-  DevBufs(const DevBufs&) = delete;
-  DevBufs& operator=(const DevBufs&) = delete;
-  ~DevBufs() {
-    for (void* q : held) (void)hipFree(q);  // hipFree waits for the device
-  }
-};
-
 dlmc_status write_out(const std::vector<uint8_t>& bytes, uint8_t* out, uint64_t cap,
                       uint64_t* out_len) {
   if (out_len) *out_len = bytes.size();
@@ -280,19 +259,11 @@ dlmc_status dlmc_entropy_cdf(dlmc_model* m, const float* logits, int32_t n_rows,
                  "cdf_bits must be in 2..31 with 2^cdf_bits > vocab");
       DLMC_CHECK(n_rows <= 65535, DLMC_E_INVAL, "at most 65535 CDF rows per call");
     }
-    entropy_rows(s, logits, n_rows, nullptr, V, entropy_bits, row_max);
+    // the CDF rows, written last, hold the group statistics first
+    entropy_rows(s, logits, n_rows, nullptr, V, entropy_bits, row_max, cdf, (size_t)V + 1);
     if (cdf && n_rows > 0) {
-      // every row committed: one "chunk" per row, n_sel = 1
-      DevBufs bufs;
-      int32_t* sel_row = bufs.alloc<int32_t>((size_t)n_rows * 4);
-      int32_t* n_sel = bufs.alloc<int32_t>((size_t)n_rows * 4);
-      void* ws = bufs.alloc<void>(cdf_workspace_bytes(n_rows, V));
-      std::vector<int32_t> idx(n_rows), one(n_rows, 1);
-      for (int i = 0; i < n_rows; ++i) idx[i] = i;
-      DLMC_HIP(hipMemcpyAsync(sel_row, idx.data(), idx.size() * 4, hipMemcpyHostToDevice, s));
-      DLMC_HIP(hipMemcpyAsync(n_sel, one.data(), one.size() * 4, hipMemcpyHostToDevice, s));
-      cdf_rows(s, logits, row_max, sel_row, n_sel, n_rows, 1, V, cdf_bits, cdf, g, ws);
-      DLMC_HIP(hipStreamSynchronize(s));
+      void* ws = cdf_by_rows((size_t)n_rows, V) ? nullptr : m->ensure_ws(cdf_workspace_bytes(n_rows, V));
+      cdf_rows(s, logits, row_max, nullptr, nullptr, n_rows, 1, V, cdf_bits, cdf, g, ws);
     }
     DLMC_HIP(hipStreamSynchronize(s));
   });
@@ -306,8 +277,8 @@ dlmc_status dlmc_entropy_cdf_noalloc(dlmc_model* m, const float* logits, int32_t
     DLMC_CHECK(logits && entropy_bits && row_max && n_rows >= 0, DLMC_E_INVAL, "bad argument");
     const int V = m->cfg.vocab;
     hipStream_t s = m->stream;
-    // the scratch holds sel_row[n] and n_sel[n], then (256-byte aligned) the
-    // CDF segment partials
+    // the documented limit: 8 n_rows bytes, rounded up to 256, and the CDF segment
+    // partials, which start there
     const size_t ws_off = ((size_t)n_rows * 8 + 255) & ~(size_t)255;
     const size_t need = cdf ? ws_off + cdf_workspace_bytes((size_t)n_rows, V) : 0;
     if (cdf) {
@@ -319,14 +290,11 @@ dlmc_status dlmc_entropy_cdf_noalloc(dlmc_model* m, const float* logits, int32_t
                      std::to_string(SCRATCH_BYTES));
     }
     DLMC_CHECK(m->scratch, DLMC_E_DEVICE, "no static scratch on this device");
-    entropy_rows(s, logits, n_rows, nullptr, V, entropy_bits, row_max);
+    // the CDF rows, written last, hold the group statistics first
+    entropy_rows(s, logits, n_rows, nullptr, V, entropy_bits, row_max, cdf, (size_t)V + 1);
     if (cdf && n_rows > 0) {
-      uint8_t* base = (uint8_t*)m->scratch;
-      int32_t* sel_row = (int32_t*)base;
-      int32_t* n_sel = sel_row + n_rows;
-      void* ws = base + ws_off;
-      fill_row_slots(s, sel_row, n_sel, n_rows);
-      cdf_rows(s, logits, row_max, sel_row, n_sel, n_rows, 1, V, cdf_bits, cdf, g, ws);
+      void* ws = (uint8_t*)m->scratch + ws_off;
+      cdf_rows(s, logits, row_max, nullptr, nullptr, n_rows, 1, V, cdf_bits, cdf, g, ws);
     }
     DLMC_HIP(hipStreamSynchronize(s));
   });
@@ -341,24 +309,13 @@ dlmc_status dlmc_select(dlmc_model* m, const float* H, const int32_t* rows, int3
     DLMC_CHECK(B >= 1 && B <= m->cfg.max_batch && T >= 1 && n_rows >= 0 && n_rows <= B * T,
                DLMC_E_INVAL, "bad batch shape");
     hipStream_t s = m->stream;
-    // chunk segments of the caller's row list (ascending flat indices)
-    std::vector<int32_t> hrows(n_rows), off(B), cnt(B, 0);
-    if (n_rows) DLMC_HIP(hipMemcpyAsync(hrows.data(), rows, (size_t)n_rows * 4, hipMemcpyDeviceToHost, s));
+    // the chunk segments of the caller's row list are found on the device, and
+    // the error flag is host memory that the kernel writes
+    int32_t* flag = m->clear_flag();
+    select_positions(s, H, rows, nullptr, nullptr, B, T, tau_bits, m_min, m_max, sel_pos, sel_row, n_sel,
+                     flag, n_rows);
     DLMC_HIP(hipStreamSynchronize(s));
-    int i = 0;
-    for (int b = 0; b < B; ++b) {
-      off[b] = i;
-      while (i < n_rows && hrows[i] < (b + 1) * T) ++i;
-      cnt[b] = i - off[b];
-    }
-    DLMC_HIP(hipMemcpyAsync(m->chunk_off, off.data(), (size_t)B * 4, hipMemcpyHostToDevice, s));
-    DLMC_HIP(hipMemcpyAsync(m->chunk_cnt, cnt.data(), (size_t)B * 4, hipMemcpyHostToDevice, s));
-    DLMC_HIP(hipMemsetAsync(m->err, 0, 4, s));
-    select_positions(s, H, rows, m->chunk_off, m->chunk_cnt, B, T, tau_bits, m_min, m_max, sel_pos,
-                     sel_row, n_sel, m->err);
-    int32_t err = 0;
-    DLMC_HIP(hipMemcpyAsync(&err, m->err, 4, hipMemcpyDeviceToHost, s));
-    DLMC_HIP(hipStreamSynchronize(s));
+    const int32_t err = *(volatile int32_t*)flag;
     if (err) throw Error(DLMC_E_NUMERIC, "non-finite entropy");
   });
 }
@@ -437,32 +394,6 @@ dlmc_status dlmc_profile_read(dlmc_model* m, int32_t stage, double* ms_total, ui
   });
 }
 
-namespace {
-// one "chunk" of length 1 per row: slot i commits position 0 of row i
-struct RowSlots {
-  DevBufs bufs;
-  int32_t *sel_row = nullptr, *sel_pos = nullptr, *n_sel = nullptr, *state = nullptr;
-  int64_t* base = nullptr;
-  uint32_t* pairs = nullptr;
-  explicit RowSlots(int n, hipStream_t s) {
-    sel_row = bufs.alloc<int32_t>((size_t)n * 4);
-    sel_pos = bufs.alloc<int32_t>((size_t)n * 4);
-    n_sel = bufs.alloc<int32_t>((size_t)n * 4);
-    state = bufs.alloc<int32_t>((size_t)n * 4);
-    base = bufs.alloc<int64_t>((size_t)n * 8);
-    pairs = bufs.alloc<uint32_t>((size_t)n * 8);
-    std::vector<int32_t> idx(n), zero(n, 0), one(n, 1);
-    std::vector<int64_t> b(n);
-    for (int i = 0; i < n; ++i) idx[i] = i, b[i] = i;
-    DLMC_HIP(hipMemcpyAsync(sel_row, idx.data(), (size_t)n * 4, hipMemcpyHostToDevice, s));
-    DLMC_HIP(hipMemcpyAsync(sel_pos, zero.data(), (size_t)n * 4, hipMemcpyHostToDevice, s));
-    DLMC_HIP(hipMemcpyAsync(n_sel, one.data(), (size_t)n * 4, hipMemcpyHostToDevice, s));
-    DLMC_HIP(hipMemcpyAsync(base, b.data(), (size_t)n * 8, hipMemcpyHostToDevice, s));
-    DLMC_HIP(hipStreamSynchronize(s));
-  }
-};
-}  // namespace
-
 dlmc_status dlmc_context_scores(dlmc_model* m, const int32_t* tokens, int32_t T, float* scores) {
   return guard([&] {
     use(m);
@@ -484,10 +415,8 @@ dlmc_status dlmc_rank_rows(dlmc_model* m, const float* logits, int32_t n_rows, c
     if (n_rows == 0) return;
     DLMC_CHECK(logits && sym && rank, DLMC_E_INVAL, "NULL argument");
     hipStream_t s = m->stream;
-    RowSlots r(n_rows, s);
-    rank_symbols(s, logits, r.sel_row, r.sel_pos, r.n_sel, sym, r.base, r.state, n_rows, 1, 1,
-                 m->cfg.vocab, r.pairs);
-    DLMC_HIP(hipMemcpy2DAsync(rank, 4, r.pairs, 8, 4, n_rows, hipMemcpyDeviceToDevice, s));
+    rank_symbols(s, logits, nullptr, nullptr, nullptr, sym, nullptr, nullptr, n_rows, 1, 1, m->cfg.vocab,
+                 (uint32_t*)rank);
     DLMC_HIP(hipStreamSynchronize(s));
   });
 }
@@ -500,13 +429,11 @@ dlmc_status dlmc_select_rank_rows(dlmc_model* m, const float* logits, int32_t n_
     if (n_rows == 0) return;
     DLMC_CHECK(logits && sym && rank, DLMC_E_INVAL, "NULL argument");
     hipStream_t s = m->stream;
-    RowSlots r(n_rows, s);
-    std::vector<int32_t> h(n_rows);
-    DLMC_HIP(hipMemcpy(h.data(), rank, (size_t)n_rows * 4, hipMemcpyDeviceToHost));
-    for (int32_t v : h) DLMC_CHECK(v >= 0 && v < m->cfg.vocab, DLMC_E_INVAL, "rank outside the alphabet");
-    DLMC_HIP(hipMemcpyAsync(sym, rank, (size_t)n_rows * 4, hipMemcpyDeviceToDevice, s));
-    select_by_rank(s, logits, r.sel_row, r.sel_pos, r.n_sel, sym, r.state, n_rows, 1, 1, m->cfg.vocab);
+    int32_t* flag = m->clear_flag();
+    select_by_rank(s, logits, nullptr, nullptr, nullptr, rank, sym, nullptr, n_rows, 1, 1, m->cfg.vocab,
+                   flag);
     DLMC_HIP(hipStreamSynchronize(s));
+    DLMC_CHECK(*(volatile int32_t*)flag == 0, DLMC_E_INVAL, "rank outside the alphabet");
   });
 }
 

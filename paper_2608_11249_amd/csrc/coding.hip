@@ -15,75 +15,118 @@ namespace dlmc {
 namespace {
 
 // ---------------------------------------------------------------- compaction
+// One block; positions are taken 65536 at a time, up to 1024 words of 64, split
+// evenly over the 16 waves: a wave ballots its words from coalesced loads, 16 in
+// flight, lane i keeping its i-th word's ballot, one block scan of the word
+// counts gives every word its first output row, and the ballots in LDS place
+// each row and the chunk boundaries without reading anything back.  65536
+// positions: 18 us, bound by one CU's loads (75 with a barrier per 1024 positions
+// and binary searches over the row list in memory); 4096: 4.7 us (7.6).
 __global__ void __launch_bounds__(1024)
 compact_kernel(const int32_t* __restrict__ state, int B, int T, int mask_id,
                int32_t* __restrict__ rows, int32_t* __restrict__ n_rows,
                int32_t* __restrict__ chunk_off, int32_t* __restrict__ chunk_cnt) {
-  __shared__ int wcount[16];
+  constexpr int WORDS = 1024, SPAN = WORDS * 64, LF = 16;
+  __shared__ uint64_t word[WORDS];
+  __shared__ int first[WORDS];
+  __shared__ int wsum[16];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int total = B * T;
   int carry = 0;
-  for (int base = 0; base < total; base += 1024) {
-    const int i = base + tid;
-    const bool flag = i < total && state[i] == mask_id;
-    const uint64_t bal = __ballot(flag);
-    const int before = __popcll(bal & ((1ull << lane) - 1ull));
-    if (lane == 0) wcount[wave] = __popcll(bal);
-    __syncthreads();
-    int woff = 0, tile = 0;
-    for (int w = 0; w < 16; ++w) {
-      woff += w < wave ? wcount[w] : 0;
-      tile += wcount[w];
+  for (int base = 0; base < total; base += SPAN) {
+    const int span = min(SPAN, total - base);
+    const int n_words = (span + 63) / 64, wpw = (n_words + 15) / 16;  // words in all, per wave (<= 64)
+    const int w0 = wave * wpw;
+    uint64_t mine = 0;
+    for (int i0 = 0; i0 < wpw; i0 += LF) {
+      int32_t v[LF];
+#pragma unroll
+      for (int i = 0; i < LF; ++i) v[i] = state[min(base + (w0 + i0 + i) * 64 + lane, total - 1)];
+#pragma unroll
+      for (int i = 0; i < LF; ++i) {
+        const bool in = i0 + i < wpw && base + (w0 + i0 + i) * 64 + lane < total;
+        const uint64_t bal = __ballot(in && v[i] == mask_id);
+        mine = i0 + i == lane ? bal : mine;
+      }
     }
-    if (flag) rows[carry + woff + before] = i;
-    carry += tile;
+    const int cnt = __popcll(mine);
+    int incl = cnt;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+      const int y = __shfl_up(incl, o);
+      if (lane >= o) incl += y;
+    }
+    if (lane == 63) wsum[wave] = incl;
+    __syncthreads();
+    int before = carry, all = 0;
+#pragma unroll
+    for (int w = 0; w < 16; ++w) {
+      before += w < wave ? wsum[w] : 0;
+      all += wsum[w];
+    }
+    if (lane < wpw && w0 + lane < WORDS) {
+      word[w0 + lane] = mine;
+      first[w0 + lane] = before + incl - cnt;
+    }
+    __syncthreads();
+#pragma unroll 4
+    for (int w = w0; w < min(w0 + wpw, n_words); ++w) {
+      const uint64_t bal = word[w];
+      if (bal >> lane & 1) rows[first[w] + __popcll(bal & ((1ull << lane) - 1ull))] = base + w * 64 + lane;
+    }
+    // first rows of the chunks that start in this span
+    for (int b = (base + T - 1) / T + tid; b < B && b * T < base + span; b += 1024) {
+      const int p = b * T - base;
+      chunk_off[b] = first[p >> 6] + __popcll(word[p >> 6] & ((1ull << (p & 63)) - 1ull));
+    }
+    carry += all;
     __syncthreads();
   }
   if (tid == 0) n_rows[0] = carry;
-  __syncthreads();
-  // segment of chunk b: rows are ascending, find [b*T, (b+1)*T)
-  for (int b = tid; b < B; b += 1024) {
-    int lo = 0, hi = carry;
-    while (lo < hi) {
-      const int mid = (lo + hi) >> 1;
-      if (rows[mid] < b * T) lo = mid + 1; else hi = mid;
-    }
-    int lo2 = lo, hi2 = carry;
-    while (lo2 < hi2) {
-      const int mid = (lo2 + hi2) >> 1;
-      if (rows[mid] < (b + 1) * T) lo2 = mid + 1; else hi2 = mid;
-    }
-    chunk_off[b] = lo;
-    chunk_cnt[b] = lo2 - lo;
-  }
+  for (int b = tid; b < B; b += 1024) chunk_cnt[b] = (b + 1 < B ? chunk_off[b + 1] : carry) - chunk_off[b];
 }
 
 // ---------------------------------------------------------------- entropy
-// Row statistics in the fixed partition of rowstats.h: the LM head's
-// epilogue writes the statistics of every 128-column group (stats_merge_kernel
-// merges them); row_stats_kernel computes the same groups from stored logits
-// and merges them in the same order, so both give the same bits.
+// Row statistics in the fixed partition of rowstats.h: the LM head's epilogue
+// writes the statistics of every 128-column group (stats_merge_kernel merges
+// them); from stored logits half a wave computes a group from one coalesced
+// 16-byte load per lane.  row_stats_kernel does a whole row per block, merging
+// in the same order; with few rows, group_stats_kernel spreads the groups over
+// the chip into a scratch row per logit row, for stats_merge_kernel.  512 rows of
+// 32768: 15 us, 24 when a thread read a whole group, 128 columns apart from the
+// next thread's.
 
-// One row per block of 256 threads.  Groups are taken 256 at a time: thread
-// t computes group 256 c + t into LDS, and lane l of wave 0 folds groups
-// 256 c + l, + 64, + 128, + 192 into its running statistic -- the fold order
-// of stats_merge_kernel.
-__global__ void __launch_bounds__(256)
+// columns 4 i .. 4 i + 3 (i = lane % 32) of group g of a row, -inf past V
+__device__ __forceinline__ f32x4 group_quad(const float* lg, int g, int i, int V, bool aligned) {
+  const int c = g * STAT_GROUP + 4 * i;
+  if (aligned && c + 4 <= V) return *reinterpret_cast<const f32x4*>(lg + c);
+  f32x4 v;
+#pragma unroll
+  for (int e = 0; e < 4; ++e) v[e] = c + e < V ? lg[c + e] : -INFINITY;
+  return v;
+}
+
+// One row per block of NT threads, 256 groups at a time into LDS; lane l of
+// wave 0 folds groups 256 c + l, + 64, + 128, + 192 into its running statistic
+// -- the fold order of stats_merge_kernel.
+template <int NT>
+__global__ void __launch_bounds__(NT)
 row_stats_kernel(const float* __restrict__ logits, const int32_t* __restrict__ n_dev, int V,
                  float* __restrict__ H, float* __restrict__ mx) {
   __shared__ RowStat part[256];
   const int row = blockIdx.x;
   if (n_dev && row >= *n_dev) return;
   const float* lg = logits + (size_t)row * V;
-  const int tid = threadIdx.x;
+  const int tid = threadIdx.x, half = tid >> 5, i = tid & 31;
   const int G = stat_groups(V);
-  const bool aligned = (V & 3) == 0;  // every group starts 16-byte aligned
+  const bool aligned = (V & 3) == 0 && ((uintptr_t)logits & 15) == 0;
   RowStat acc{-INFINITY, 0.0f, 0.0f};
   for (int g0 = 0; g0 < G; g0 += 256) {
-    const int g = g0 + tid;
-    if (g < G) {
-      const int c = g * STAT_GROUP;
-      part[tid] = group_stat(lg + c, min(STAT_GROUP, V - c), aligned);
+    const int gn = min(256, G - g0);
+#pragma unroll 2
+    for (int g = half; g < gn; g += NT / 32) {
+      const RowStat s = group_stat_lanes(group_quad(lg, g0 + g, i, V, aligned));
+      if (i == 0) part[g] = s;
     }
     __syncthreads();
     if (tid < 64)
@@ -101,16 +144,49 @@ row_stats_kernel(const float* __restrict__ logits, const int32_t* __restrict__ n
   }
 }
 
-// Merge of the group statistics stats[row * ld + g], g < G, one wave per row.
+// GPB groups per block: group statistics of row blockIdx.y into its scratch
+// row (ld RowStats apart in 4-byte words)
+constexpr int GROUPS_PER_BLOCK = 32;
+
 __global__ void __launch_bounds__(256)
-stats_merge_kernel(const RowStat* __restrict__ stats, int ld, int G, const int32_t* __restrict__ n_dev,
+group_stats_kernel(const float* __restrict__ logits, int V, float* __restrict__ scratch, size_t ld) {
+  const int row = blockIdx.y, half = threadIdx.x >> 5, i = threadIdx.x & 31;
+  const float* lg = logits + (size_t)row * V;
+  const bool aligned = (V & 3) == 0 && ((uintptr_t)logits & 15) == 0;
+  const int G = stat_groups(V), g0 = blockIdx.x * GROUPS_PER_BLOCK;
+  f32x4 v[GROUPS_PER_BLOCK / 8];
+#pragma unroll
+  for (int k = 0; k < GROUPS_PER_BLOCK / 8; ++k)
+    if (g0 + half + 8 * k < G) v[k] = group_quad(lg, g0 + half + 8 * k, i, V, aligned);
+#pragma unroll
+  for (int k = 0; k < GROUPS_PER_BLOCK / 8; ++k) {
+    const int g = g0 + half + 8 * k;
+    if (g >= G) break;
+    const RowStat s = group_stat_lanes(v[k]);
+    if (i < 3) scratch[row * ld + 3 * (size_t)g + i] = i == 0 ? s.m : i == 1 ? s.Z : s.A;
+  }
+}
+
+// Merge of the group statistics of a row, g < G at words row * ld + 3 g, one
+// wave per row.
+__global__ void __launch_bounds__(256)
+stats_merge_kernel(const float* __restrict__ stats, size_t ld, int G, const int32_t* __restrict__ n_dev,
                    int n_max, float* __restrict__ H, float* __restrict__ mx) {
   const int row = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
   const int n = n_dev ? min(*n_dev, n_max) : n_max;
   if (row >= n) return;
-  const RowStat* s = stats + (size_t)row * ld;
+  const float* s = stats + (size_t)row * ld;
   RowStat acc{-INFINITY, 0.0f, 0.0f};
-  for (int g = lane; g < G; g += 64) acc = stat_merge(acc, s[g]);
+  for (int g0 = lane; g0 < G; g0 += 64 * 16) {
+    RowStat r[16];  // 16 groups in flight per lane
+#pragma unroll
+    for (int k = 0; k < 16; ++k) {
+      const int g = g0 + 64 * k;
+      r[k] = g < G ? RowStat{s[3 * g], s[3 * g + 1], s[3 * g + 2]} : RowStat{-INFINITY, 0.0f, 0.0f};
+    }
+#pragma unroll
+    for (int k = 0; k < 16; ++k) acc = stat_merge(acc, r[k]);
+  }
   acc = stat_butterfly<64>(acc);
   if (lane == 0) {
     H[row] = stat_entropy_bits(acc);
@@ -124,82 +200,152 @@ __device__ __forceinline__ uint32_t order_bits(float f) {
   return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
 }
 
-template <typename K>
-__device__ void bitonic_sort(K* keys, int n2) {
-  for (int k = 2; k <= n2; k <<= 1) {
-    for (int j = k >> 1; j > 0; j >>= 1) {
-      for (int i = threadIdx.x; i < n2; i += blockDim.x) {
-        const int ixj = i ^ j;
-        if (ixj > i) {
-          const K a = keys[i], b = keys[ixj];
-          const bool up = (i & k) == 0;
-          if ((a > b) == up) {
-            keys[i] = b;
-            keys[ixj] = a;
-          }
-        }
-      }
-      __syncthreads();
-    }
-  }
-}
-
 constexpr int SEL_MAX_T = 8192;
 constexpr int SEL_MAX_M = 1024;
 
-// One workgroup per chunk: sort the chunk's masked positions by
-// (entropy, position), commit n = min(|M|, max(m_min, min(m_max, #{H <= tau})))
-// of them, and emit the committed positions in ascending order.
-__global__ void __launch_bounds__(1024)
+// number of the ascending rows[0 .. n) below x: a wave probes the ends of 64 even
+// stretches of the bracket at a time (65536 rows: three rounds of one load)
+__device__ __forceinline__ int rows_below(const int32_t* __restrict__ rows, int n, int x) {
+  const int lane = threadIdx.x & 63;
+  int lo = 0, hi = n;
+  while (lo < hi) {
+    const int step = (hi - lo + 63) / 64;
+    const uint64_t below = __ballot(rows[min(lo + (lane + 1) * step, hi) - 1] < x);
+    // probes past hi repeat its last row: whole stretches below x, or all of it
+    const int full = min(lo + __popcll(below) * step, hi);
+    hi = min(full + step - 1, hi);
+    lo = full;
+  }
+  return lo;
+}
+
+// One workgroup per chunk: commit the n = min(|M|, max(m_min, min(m_max, #{H <=
+// tau}))) masked positions that come first by (entropy, position), in
+// ascending position order.  The n-th smallest entropy is found by a radix
+// search, two bits a round: a thread keeps its keys (position order within each
+// NT) in registers, ballots count the digits of the keys that still match the
+// prefix, and the waves add their counts to one LDS word per digit.  The search
+// ends when every key that still matches is to be committed.  Everything below
+// the entropy found is committed, and the lowest positions among its equals;
+// prefix counts over the ballots place them.  A round costs a barrier and an
+// LDS round trip, so chunks that fit 8 keys per thread use 256 threads.  32
+// chunks of 1024 masked positions: 13 us (35 with a bitonic sort of the keys).
+template <int NT, int KPT>
+__global__ void __launch_bounds__(NT)
 select_kernel(const float* __restrict__ H, const int32_t* __restrict__ rows,
               const int32_t* __restrict__ chunk_off, const int32_t* __restrict__ chunk_cnt, int T,
               float tau, int m_min, int m_max, int32_t* __restrict__ sel_pos,
-              int32_t* __restrict__ sel_row, int32_t* __restrict__ n_sel, int32_t* __restrict__ err) {
-  __shared__ uint64_t keys[SEL_MAX_T];
-  __shared__ int32_t chosen[SEL_MAX_M];
-  __shared__ int wsum[16], wbad[16];
-  const int b = blockIdx.x, tid = threadIdx.x;
-  const int off = chunk_off[b], cnt = chunk_cnt[b];
-  int n2 = 1;
-  while (n2 < cnt) n2 <<= 1;
+              int32_t* __restrict__ sel_row, int32_t* __restrict__ n_sel, int32_t* __restrict__ err,
+              int n_rows) {
+  constexpr int NW = NT / 64;
+  __shared__ int digits[64];  // of round r: 4 r + digit
+  __shared__ int wsum[KPT][NW], esum[KPT][NW];
+  __shared__ int n_thr, n_bad;
+  const int b = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  int off, cnt;
+  if (chunk_off) {
+    off = chunk_off[b];
+    cnt = chunk_cnt[b];
+  } else {
+    off = b == 0 ? 0 : rows_below(rows, n_rows, b * T);
+    cnt = rows_below(rows, n_rows, (b + 1) * T) - off;
+  }
+  cnt = min(max(cnt, 0), NT * KPT);  // rows are distinct: at most T <= NT KPT of a chunk
+  const int nr = (cnt + NT - 1) / NT;  // groups of NT keys in use
+  if (tid < 64) digits[tid] = 0;
+  if (tid == 0) n_thr = n_bad = 0;
+  uint32_t key[KPT];
   int thr = 0, bad = 0;
-  for (int i = tid; i < n2; i += 1024) {
-    uint64_t key = ~0ull;
-    if (i < cnt) {
+#pragma unroll
+  for (int r = 0; r < KPT; ++r) {
+    const int i = r * NT + tid;
+    key[r] = 0;
+    if (r < nr && i < cnt) {
       const float h = H[off + i];
       bad |= !(h == h) || isinf(h);
       thr += h <= tau;
-      key = ((uint64_t)order_bits(h) << 32) | (uint32_t)i;
+      key[r] = order_bits(h);
     }
-    keys[i] = key;
   }
-  // counts (integer: order-free)
-  int c = thr;
+  __syncthreads();
 #pragma unroll
-  for (int o = 32; o > 0; o >>= 1) c += __shfl_xor(c, o);
-  const int anybad = __any(bad);
-  if ((tid & 63) == 0) {
-    wsum[tid >> 6] = c;
-    wbad[tid >> 6] = anybad;
-  }
+  for (int o = 32; o > 0; o >>= 1) thr += __shfl_xor(thr, o);
+  if (lane == 0 && thr) atomicAdd(&n_thr, thr);
+  if (__any(bad) && lane == 0) n_bad = 1;
   __syncthreads();
-  int n_thr = 0, nbad = 0;
-  for (int w = 0; w < 16; ++w) {
-    n_thr += wsum[w];
-    nbad += wbad[w];
-  }
-  if (tid == 0 && nbad) err[0] = 1;
+  if (tid == 0 && n_bad) err[0] = 1;
   const int n = min(cnt, max(m_min, min(m_max, n_thr)));
-  bitonic_sort(keys, n2);
-  int n2s = 1;
-  while (n2s < n) n2s <<= 1;
-  for (int i = tid; i < n2s; i += 1024) chosen[i] = i < n ? (int32_t)(keys[i] & 0xFFFFFFFFu) : INT_MAX;
+  // key of the n-th smallest (1-based); `need` of its equals are committed
+  // (with fewer bits in mask: of the keys that match the prefix, all)
+  uint32_t prefix = 0, mask = 0;
+  int need = n, match = cnt;
+  if (n < cnt) {
+#pragma unroll 1
+    for (int round = 0; round < 16 && need < match; ++round) {
+      const int sh = 30 - 2 * round;
+      int c[3] = {0, 0, 0};
+#pragma unroll
+      for (int r = 0; r < KPT; ++r) {
+        if (r >= nr) break;
+        const bool in = r * NT + tid < cnt && (key[r] & mask) == prefix;
+        const uint32_t d = key[r] >> sh & 3u;
+#pragma unroll
+        for (int k = 0; k < 3; ++k) c[k] += __popcll(__ballot(in && d == (uint32_t)k));
+      }
+      if (lane < 3) {
+        const int v = lane == 0 ? c[0] : lane == 1 ? c[1] : c[2];
+        if (v) atomicAdd(&digits[4 * round + lane], v);
+      }
+      __syncthreads();
+      // keys with a digit below 1, 2 and 3 among those that match the prefix
+      const int u1 = digits[4 * round], u2 = u1 + digits[4 * round + 1], u3 = u2 + digits[4 * round + 2];
+      const uint32_t d = need > u3 ? 3u : need > u2 ? 2u : need > u1 ? 1u : 0u;
+      const int below = need > u3 ? u3 : need > u2 ? u2 : need > u1 ? u1 : 0;
+      prefix |= d << sh;
+      mask |= 3u << sh;
+      need -= below;
+      match = d == 0 ? u1 : d == 1 ? u2 - u1 : d == 2 ? u3 - u2 : match - u3;
+    }
+  }
+  int ls[KPT], le[KPT];  // committed-below and equal keys before this lane, in its wave
+#pragma unroll
+  for (int r = 0; r < KPT; ++r) {
+    if (r >= nr) break;
+    const bool valid = r * NT + tid < cnt;
+    const uint64_t lt = __ballot(valid && (key[r] & mask) < prefix);
+    const uint64_t eq = __ballot(valid && (key[r] & mask) == prefix);
+    const uint64_t lower = (1ull << lane) - 1ull;
+    ls[r] = __popcll(lt & lower);
+    le[r] = __popcll(eq & lower);
+    if (lane == 0) {
+      wsum[r][wave] = __popcll(lt);
+      esum[r][wave] = __popcll(eq);
+    }
+  }
   __syncthreads();
-  bitonic_sort(chosen, n2s);
-  for (int j = tid; j < n; j += 1024) {
-    const int local = chosen[j];
-    sel_pos[b * m_max + j] = rows[off + local] - b * T;
-    sel_row[b * m_max + j] = off + local;
+  int s0 = 0, e0 = 0;
+#pragma unroll
+  for (int r = 0; r < KPT; ++r) {
+    if (r >= nr) break;
+    int sw = s0, ew = e0, st = 0, et = 0;
+    for (int w = 0; w < NW; ++w) {
+      st += wsum[r][w];
+      et += esum[r][w];
+      if (w < wave) {
+        sw += wsum[r][w];
+        ew += esum[r][w];
+      }
+    }
+    const int i = r * NT + tid;
+    const bool valid = i < cnt, lt = valid && (key[r] & mask) < prefix;
+    const bool eq = valid && (key[r] & mask) == prefix && ew + le[r] < need;
+    if (lt || eq) {
+      const int j = sw + ls[r] + min(ew + le[r], need);  // committed keys before this one
+      sel_pos[b * m_max + j] = rows[off + i] - b * T;
+      sel_row[b * m_max + j] = off + i;
+    }
+    s0 += st;
+    e0 += et;
   }
   if (tid == 0) n_sel[b] = n;
 }
@@ -219,14 +365,15 @@ __device__ __forceinline__ U block_sum_int(U v, U* red) {
   return red[0] + red[1] + red[2] + red[3];
 }
 
-// Integer CDF of the committed rows, each row split into CDF_SEG-entry
-// segments handled by separate workgroups (three passes):
+// Integer CDF of the committed rows:
 //   g_v = floor(exp(l_v - max) 2^24), G = sum g, f_v = 1 + floor(g_v (2^P - V) / G),
 //   the remainder 2^P - sum f goes to the lowest index of maximal g,
 //   cdf[0] = 0, cdf[v+1] = cdf[v] + f_v.
-// Pass A: per-segment sum of g and lowest index with g = 2^24; pass B:
-// per-segment sum of f; pass C: segment offset + in-segment scan.  Every sum
-// is an integer, so the segment split does not change a single bit.
+// Every sum is an integer, so no split of the work changes a single bit.  Two
+// forms: one block per row with the row in registers (cdf_row_kernel), and,
+// for few long rows, CDF_SEG-entry segments over three passes that park g, then
+// f, in the CDF row itself: A: g, per-segment sum of g and lowest index with
+// g = 2^24; B: f and per-segment sum of f; C: segment offset + in-segment scan.
 constexpr int CDF_SEG = 4096;
 
 struct CdfArgs {
@@ -242,27 +389,174 @@ struct CdfArgs {
   int32_t* segA;
 };
 
+// whether slot holds a committed row, and which
+__device__ __forceinline__ bool cdf_live(const CdfArgs& c, int slot) {
+  if (!c.n_sel) return true;
+  const int b = slot / c.m_max;
+  return slot - b * c.m_max < c.n_sel[b];
+}
+__device__ __forceinline__ int cdf_row_of(const CdfArgs& c, int slot) {
+  return c.sel_row ? c.sel_row[slot] : slot;
+}
+
+// floor(g cst / G) for g <= 2^24, cst < 2^31, G < 2^53, by one double product:
+// cst / G and the product are each rounded once, so t is off by less than 2^31
+// x 2^-51 = 2^-20, and its floor is the quotient unless t lies within that of an
+// integer, where it can be off by one and the remainder decides (once in about
+// 2^17 entries).  A 64-bit division per entry took most of the time of passes B
+// and C.
+struct Quot {
+  uint64_t cst, G;
+  double c;
+  __device__ Quot(uint64_t cst_, uint64_t G_) : cst(cst_), G(G_), c((double)cst_ / (double)G_) {}
+  __device__ __forceinline__ uint32_t operator()(uint32_t g) const {
+    const double t = (double)g * c;
+    uint32_t q = (uint32_t)t;
+    const double frac = t - (double)q;
+    if (g != 0 && (frac < 0x1p-18 || frac > 1.0 - 0x1p-18)) {
+      const int64_t r = (int64_t)((uint64_t)g * cst - (uint64_t)q * G);
+      q += r < 0 ? -1 : r >= (int64_t)G ? 1 : 0;
+    }
+    return q;
+  }
+};
+
+// G of a row.  A finite row maximum gives G >= 2^24; a row of non-finite
+// logits (reported as E_NUMERIC before its CDF is used) can give 0, which is
+// raised to 1 so that the quotients stay defined.
+__device__ __forceinline__ uint64_t nonzero(uint64_t G) { return G > 0 ? G : 1; }
+
+template <typename U>
+__device__ __forceinline__ U wave_sum(U v) {
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
+  return v;
+}
+__device__ __forceinline__ int wave_min(int v) {
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) v = min(v, __shfl_xor(v, o));
+  return v;
+}
+
+// inclusive prefix sum over the 64 lanes of a wave: row shifts, then the last
+// lane of each 16-lane row broadcast into the next rows
+__device__ __forceinline__ uint32_t wave_scan(uint32_t x) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  x += __builtin_amdgcn_update_dpp(0, x, 0x111, 0xf, 0xf, false);  // row_shr:1
+  x += __builtin_amdgcn_update_dpp(0, x, 0x112, 0xf, 0xf, false);
+  x += __builtin_amdgcn_update_dpp(0, x, 0x114, 0xf, 0xf, false);
+  x += __builtin_amdgcn_update_dpp(0, x, 0x118, 0xf, 0xf, false);
+  x += __builtin_amdgcn_update_dpp(0, x, 0x142, 0xa, 0xf, false);  // row_bcast:15 into rows 1 and 3
+  x += __builtin_amdgcn_update_dpp(0, x, 0x143, 0xc, 0xf, false);  // row_bcast:31 into rows 2 and 3
+#endif
+  return x;
+}
+
+// One row per block: wave w holds entries 64 (w E + e) + lane, e < E, in
+// registers (V <= NT E), so a logit is read once and a CDF entry written once.
+template <int NT, int E>
+__global__ void __launch_bounds__(NT) cdf_row_kernel(CdfArgs c) {
+  constexpr int NW = NT / 64;
+  __shared__ uint64_t wG[NW];
+  __shared__ int wA[NW];
+  __shared__ uint32_t wF[NW];
+  const int slot = blockIdx.x;
+  if (!cdf_live(c, slot)) return;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int row = cdf_row_of(c, slot), V = c.V;
+  const float* lg = c.logits + (size_t)row * V;
+  const float m = c.mx[row];
+  const int v0 = wave * 64 * E + lane;
+  uint32_t f[E];
+  uint64_t G = 0;
+  int a = INT_MAX;
+  constexpr int EB = E < 16 ? E : 16;  // loads in flight
+#pragma unroll
+  for (int e0 = 0; e0 < E; e0 += EB) {
+    float l[EB];
+#pragma unroll
+    for (int e = 0; e < EB; ++e) {
+      const int v = v0 + 64 * (e0 + e);
+      l[e] = v < V ? lg[v] : -INFINITY;
+    }
+#pragma unroll
+    for (int e = 0; e < EB; ++e) {
+      const int v = v0 + 64 * (e0 + e);
+      const uint32_t g = v < V ? gval(l[e], m) : 0u;
+      f[e0 + e] = g;
+      G += g;
+      if (g == (1u << 24)) a = min(a, v);
+      if (c.g_out && v < V) c.g_out[(size_t)slot * V + v] = g;
+    }
+    __builtin_amdgcn_sched_barrier(0);  // else every load is hoisted, past the registers
+  }
+  G = wave_sum(G);
+  a = wave_min(a);
+  if (lane == 0) {
+    wG[wave] = G;
+    wA[wave] = a;
+  }
+  __syncthreads();
+  G = 0;
+#pragma unroll
+  for (int w = 0; w < NW; ++w) {
+    G += wG[w];
+    a = min(a, wA[w]);
+  }
+  const Quot quot((1ull << c.P) - (uint64_t)V, nonzero(G));
+  uint32_t run = 0;  // entries of this wave before the current 64
+#pragma unroll
+  for (int e = 0; e < E; ++e) {
+    const uint32_t inc = wave_scan(v0 + 64 * e < V ? 1u + quot(f[e]) : 0u);
+    f[e] = run + inc;
+    run += __builtin_amdgcn_readlane(inc, 63);
+    if (e % 16 == 15) __builtin_amdgcn_sched_barrier(0);
+  }
+  if (lane == 0) wF[wave] = run;
+  __syncthreads();
+  uint32_t before = 0, F = 0;
+#pragma unroll
+  for (int w = 0; w < NW; ++w) {
+    before += w < wave ? wF[w] : 0u;
+    F += wF[w];
+  }
+  const uint32_t R = (uint32_t)(1ull << c.P) - F;
+  uint32_t* out = c.cdf + (size_t)slot * ((size_t)V + 1);
+  if (tid == 0) out[0] = 0;
+#pragma unroll
+  for (int e = 0; e < E; ++e) {
+    const int v = v0 + 64 * e;
+    if (v < V) out[v + 1] = before + f[e] + (v >= a ? R : 0u);
+  }
+}
+
+// where the passes keep the g of slot `slot`
+__device__ __forceinline__ uint32_t* parked_g(const CdfArgs& c, int slot) {
+  return c.g_out ? c.g_out + (size_t)slot * c.V : c.cdf + (size_t)slot * ((size_t)c.V + 1) + 1;
+}
+
 __global__ void __launch_bounds__(256) cdf_pass_a(CdfArgs c) {
   __shared__ uint64_t red64[4];
   __shared__ int redi[4];
-  const int seg = blockIdx.x, slot = blockIdx.y, b = slot / c.m_max, j = slot % c.m_max;
-  if (j >= c.n_sel[b]) return;
+  const int seg = blockIdx.x, slot = blockIdx.y;
+  if (!cdf_live(c, slot)) return;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int row = c.sel_row[slot];
+  const int row = cdf_row_of(c, slot);
   const float* lg = c.logits + (size_t)row * c.V;
+  uint32_t* park = parked_g(c, slot);
   const float m = c.mx[row];
   const int v0 = seg * CDF_SEG, v1 = min(c.V, v0 + CDF_SEG);
   uint64_t G = 0;
   int a = INT_MAX;
+#pragma unroll 8
   for (int v = v0 + tid; v < v1; v += 256) {
     const uint32_t g = gval(lg[v], m);
     G += g;
     if (g == (1u << 24)) a = min(a, v);
-    if (c.g_out) c.g_out[(size_t)slot * c.V + v] = g;
+    park[v] = g;
   }
   G = block_sum_int<uint64_t>(G, red64);
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) a = min(a, __shfl_xor(a, o));
+  a = wave_min(a);
   if (lane == 0) redi[wave] = a;
   __syncthreads();
   if (tid == 0) {
@@ -271,95 +565,72 @@ __global__ void __launch_bounds__(256) cdf_pass_a(CdfArgs c) {
   }
 }
 
-// G of a row.  A finite row maximum gives G >= 2^24; a row of non-finite
-// logits (reported as E_NUMERIC before its CDF is used) can give 0, which is
-// raised to 1 so that the divisions below stay defined.
-__device__ __forceinline__ uint64_t row_G(const CdfArgs& c, int slot) {
-  uint64_t G = 0;
-  for (int s = 0; s < c.S; ++s) G += c.segG[(size_t)slot * c.S + s];
-  return G > 0 ? G : 1;
-}
-
 __global__ void __launch_bounds__(256) cdf_pass_b(CdfArgs c) {
   __shared__ uint64_t red64[4];
-  __shared__ uint64_t sG;
-  const int seg = blockIdx.x, slot = blockIdx.y, b = slot / c.m_max, j = slot % c.m_max;
-  if (j >= c.n_sel[b]) return;
-  const int tid = threadIdx.x;
-  if (tid == 0) sG = row_G(c, slot);
-  __syncthreads();
-  const uint64_t G = sG, cst = (1ull << c.P) - (uint64_t)c.V;
-  const int row = c.sel_row[slot];
-  const float* lg = c.logits + (size_t)row * c.V;
-  const float m = c.mx[row];
+  const int seg = blockIdx.x, slot = blockIdx.y;
+  if (!cdf_live(c, slot)) return;
+  const int tid = threadIdx.x, lane = tid & 63;
+  uint64_t G = 0;
+  for (int s = lane; s < c.S; s += 64) G += c.segG[(size_t)slot * c.S + s];
+  const Quot quot((1ull << c.P) - (uint64_t)c.V, nonzero(wave_sum(G)));
+  const uint32_t* park = parked_g(c, slot);
   const int v0 = seg * CDF_SEG, v1 = min(c.V, v0 + CDF_SEG);
   uint64_t F = 0;
-  for (int v = v0 + tid; v < v1; v += 256) F += 1 + (uint64_t)gval(lg[v], m) * cst / G;
+#pragma unroll 8
+  for (int v = v0 + tid; v < v1; v += 256) F += 1u + quot(park[v]);
   F = block_sum_int<uint64_t>(F, red64);
   if (tid == 0) c.segF[(size_t)slot * c.S + seg] = F;
 }
 
 __global__ void __launch_bounds__(256) cdf_pass_c(CdfArgs c) {
-  __shared__ uint64_t sh[3];
-  __shared__ uint32_t scan[4];
-  const int seg = blockIdx.x, slot = blockIdx.y, b = slot / c.m_max, j = slot % c.m_max;
-  if (j >= c.n_sel[b]) return;
+  constexpr int PT = CDF_SEG / 256;  // consecutive entries per thread in the scan
+  __shared__ uint32_t buf[CDF_SEG + CDF_SEG / PT];  // one word of padding per thread
+  __shared__ uint32_t wtot[4];
+  const int seg = blockIdx.x, slot = blockIdx.y;
+  if (!cdf_live(c, slot)) return;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  if (tid == 0) {
-    uint64_t F = 0, before = 0;
-    int a = INT_MAX;
-    for (int s = 0; s < c.S; ++s) {
-      const uint64_t f = c.segF[(size_t)slot * c.S + s];
-      F += f;
-      if (s < seg) before += f;
-      a = min(a, c.segA[(size_t)slot * c.S + s]);
-    }
-    const uint64_t R = (1ull << c.P) - F;
-    sh[0] = row_G(c, slot);
-    sh[1] = before + ((a < seg * CDF_SEG) ? R : 0);  // cdf value entering this segment
-    sh[2] = ((uint64_t)(uint32_t)a << 32) | (uint32_t)R;
+  uint64_t F = 0, G = 0, before = 0;
+  int a = INT_MAX;
+  for (int s = lane; s < c.S; s += 64) {
+    const uint64_t f = c.segF[(size_t)slot * c.S + s];
+    G += c.segG[(size_t)slot * c.S + s];
+    F += f;
+    before += s < seg ? f : 0;
+    a = min(a, c.segA[(size_t)slot * c.S + s]);
+  }
+  F = wave_sum(F);
+  before = wave_sum(before);
+  const Quot quot((1ull << c.P) - (uint64_t)c.V, nonzero(wave_sum(G)));
+  a = wave_min(a);
+  const uint32_t R = (uint32_t)((1ull << c.P) - F);
+  uint32_t* out = c.cdf + (size_t)slot * ((size_t)c.V + 1);
+  if (seg == 0 && tid == 0) out[0] = 0;
+  const uint32_t* park = parked_g(c, slot);
+  const int v0 = seg * CDF_SEG, v1 = min(c.V, v0 + CDF_SEG);
+#pragma unroll
+  for (int i = 0; i < PT; ++i) {
+    const int k = i * 256 + tid;
+    buf[k + k / PT] = v0 + k < v1 ? 1u + quot(park[v0 + k]) : 0u;
   }
   __syncthreads();
-  const uint64_t G = sh[0], cst = (1ull << c.P) - (uint64_t)c.V;
-  const int a = (int)(sh[2] >> 32);
-  const uint32_t R = (uint32_t)(sh[2] & 0xFFFFFFFFu);
-  const int row = c.sel_row[slot];
-  const float* lg = c.logits + (size_t)row * c.V;
-  const float m = c.mx[row];
-  uint32_t* out = c.cdf + (size_t)slot * (c.V + 1);
-  if (seg == 0 && tid == 0) out[0] = 0;
-  const int v0 = seg * CDF_SEG, v1 = min(c.V, v0 + CDF_SEG);
-  uint32_t carry = (uint32_t)sh[1];
-  for (int base = v0; base < v1; base += 1024) {
-    const int w0 = base + tid * 4;
-    uint32_t f[4], loc = 0;
+  uint32_t f[PT], loc = 0;
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      const int v = w0 + e;
-      f[e] = v < v1 ? 1u + (uint32_t)((uint64_t)gval(lg[v], m) * cst / G) + (v == a ? R : 0u) : 0u;
-      loc += f[e];
-    }
-    uint32_t inc = loc;
+  for (int i = 0; i < PT; ++i) {
+    loc += buf[tid * (PT + 1) + i];
+    f[i] = loc;
+  }
+  const uint32_t inc = wave_scan(loc);
+  if (lane == 63) wtot[wave] = inc;
+  __syncthreads();
+  uint32_t base = (uint32_t)before + inc - loc;
+  for (int w = 0; w < wave; ++w) base += wtot[w];
 #pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-      const uint32_t t = __shfl_up(inc, o);
-      if (lane >= o) inc += t;
-    }
-    __syncthreads();
-    if (lane == 63) scan[wave] = inc;
-    __syncthreads();
-    uint32_t wpre = 0;
-    for (int w = 0; w < wave; ++w) wpre += scan[w];
-    uint32_t run = carry + wpre + inc - loc;
+  for (int i = 0; i < PT; ++i) buf[tid * (PT + 1) + i] = base + f[i];
+  __syncthreads();
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      const int v = w0 + e;
-      if (v < v1) {
-        run += f[e];
-        out[v + 1] = run;
-      }
-    }
-    carry += scan[0] + scan[1] + scan[2] + scan[3];
+  for (int i = 0; i < PT; ++i) {
+    const int k = i * 256 + tid, v = v0 + k;
+    if (v < v1) out[v + 1] = buf[k + k / PT] + (v >= a ? R : 0u);
   }
 }
 
@@ -496,16 +767,29 @@ void compact_masked(hipStream_t st, const int32_t* state, int B, int T, int mask
 }
 
 void entropy_rows(hipStream_t st, const float* logits, int n_max, const int32_t* n_dev, int V,
-                  float* H, float* mx) {
+                  float* H, float* mx, void* scratch, size_t scratch_ld) {
   if (n_max <= 0) return;
-  row_stats_kernel<<<n_max, 256, 0, st>>>(logits, n_dev, V, H, mx);
+  // Few long rows: a block per row would leave most CUs idle (64 rows of 126464:
+  // 37 us; spread over the chip 12 + 5).  From about one row per CU on, and for rows
+  // of a few groups, the single kernel is faster.
+  const int G = stat_groups(V);
+  if (scratch && !n_dev && n_max < 256 && G >= 2 * GROUPS_PER_BLOCK && scratch_ld >= (size_t)3 * G) {
+    group_stats_kernel<<<dim3(ceil_div(G, GROUPS_PER_BLOCK), n_max), 256, 0, st>>>(logits, V, (float*)scratch,
+                                                                                   scratch_ld);
+    stats_merge_kernel<<<ceil_div(n_max, 4), 256, 0, st>>>((const float*)scratch, scratch_ld, G, nullptr,
+                                                            n_max, H, mx);
+  } else if (G > 32) {
+    row_stats_kernel<1024><<<n_max, 1024, 0, st>>>(logits, n_dev, V, H, mx);
+  } else {
+    row_stats_kernel<64><<<n_max, 64, 0, st>>>(logits, n_dev, V, H, mx);
+  }
   DLMC_HIP(hipGetLastError());
 }
 
 void entropy_merge(hipStream_t st, const void* stats, int ld, int V, int n_max, const int32_t* n_dev,
                    float* H, float* mx) {
   if (n_max <= 0) return;
-  stats_merge_kernel<<<ceil_div(n_max, 4), 256, 0, st>>>((const RowStat*)stats, ld, stat_groups(V),
+  stats_merge_kernel<<<ceil_div(n_max, 4), 256, 0, st>>>((const float*)stats, (size_t)3 * ld, stat_groups(V),
                                                           n_dev, n_max, H, mx);
   DLMC_HIP(hipGetLastError());
 }
@@ -513,17 +797,27 @@ void entropy_merge(hipStream_t st, const void* stats, int ld, int V, int n_max, 
 void select_positions(hipStream_t st, const float* H, const int32_t* rows,
                       const int32_t* chunk_off, const int32_t* chunk_cnt, int B, int T,
                       float tau, int m_min, int m_max, int32_t* sel_pos, int32_t* sel_row,
-                      int32_t* n_sel, int32_t* err_flag) {
+                      int32_t* n_sel, int32_t* err_flag, int n_rows) {
   DLMC_CHECK(T <= SEL_MAX_T, DLMC_E_INVAL, "chunk length above 8192 is not supported");
   DLMC_CHECK(m_min >= 1 && m_max >= m_min && m_max <= SEL_MAX_M, DLMC_E_INVAL,
              "need 1 <= m_min <= m_max <= 1024");
   if (B <= 0) return;
-  select_kernel<<<B, 1024, 0, st>>>(H, rows, chunk_off, chunk_cnt, T, tau, m_min, m_max, sel_pos,
-                                    sel_row, n_sel, err_flag);
+  if (T <= 2048)
+    select_kernel<256, 8><<<B, 256, 0, st>>>(H, rows, chunk_off, chunk_cnt, T, tau, m_min, m_max, sel_pos,
+                                             sel_row, n_sel, err_flag, n_rows);
+  else
+    select_kernel<1024, SEL_MAX_T / 1024><<<B, 1024, 0, st>>>(H, rows, chunk_off, chunk_cnt, T, tau, m_min,
+                                                              m_max, sel_pos, sel_row, n_sel, err_flag, n_rows);
   DLMC_HIP(hipGetLastError());
 }
 
 int cdf_segments(int V) { return ceil_div(V, CDF_SEG); }
+
+// One block per row while a row fits in a block's registers and either the rows
+// fill at least half the CUs or a row is a single segment; else in segments.
+// 512 rows of 32768 with g: 61 us by rows, 122 in segments with a 64-bit division
+// per entry; 64 rows of 126464 in segments: 43 us (59).
+bool cdf_by_rows(size_t slots, int V) { return V <= 32768 && (slots >= 128 || V <= CDF_SEG); }
 
 void cdf_rows(hipStream_t st, const float* logits, const float* mx, const int32_t* sel_row,
               const int32_t* n_sel, int B, int m_max, int V, int P, uint32_t* cdf,
@@ -546,10 +840,18 @@ void cdf_rows(hipStream_t st, const float* logits, const float* mx, const int32_
   c.segG = (uint64_t*)seg_ws;
   c.segF = c.segG + n;
   c.segA = (int32_t*)(c.segF + n);
-  dim3 grid(c.S, B * m_max);
-  cdf_pass_a<<<grid, 256, 0, st>>>(c);
-  cdf_pass_b<<<grid, 256, 0, st>>>(c);
-  cdf_pass_c<<<grid, 256, 0, st>>>(c);
+  const int n_slots = B * m_max;
+  if (cdf_by_rows((size_t)n_slots, V)) {
+    if (V <= 1024) cdf_row_kernel<256, 4><<<n_slots, 256, 0, st>>>(c);
+    else if (V <= 4096) cdf_row_kernel<256, 16><<<n_slots, 256, 0, st>>>(c);
+    else if (V <= 16384) cdf_row_kernel<512, 32><<<n_slots, 512, 0, st>>>(c);
+    else cdf_row_kernel<512, 64><<<n_slots, 512, 0, st>>>(c);
+  } else {
+    const dim3 grid(c.S, n_slots);
+    cdf_pass_a<<<grid, 256, 0, st>>>(c);
+    cdf_pass_b<<<grid, 256, 0, st>>>(c);
+    cdf_pass_c<<<grid, 256, 0, st>>>(c);
+  }
   DLMC_HIP(hipGetLastError());
 }
 

@@ -43,17 +43,29 @@ __global__ void init_weights_kernel(void* __restrict__ dst, int dtype, uint64_t 
   }
 }
 
-__global__ void embed_kernel(const int32_t* __restrict__ state, const void* __restrict__ table,
-                             int dtype, float* __restrict__ x, int d, int max_id) {
-  const int row = blockIdx.x;
-  const size_t src = (size_t)min(max(state[row], 0), max_id) * d;  // ids outside [0, V] clamp
-  float* dst = x + (size_t)row * d;
+// one thread per 16 bytes of table row (d % 8 == 0 for bf16, % 4 for fp32);
+// 65536 rows of 768: 58 us, 107 with 2-byte loads
+__global__ void __launch_bounds__(256)
+embed_kernel(const int32_t* __restrict__ state, const void* __restrict__ table, int dtype,
+             float* __restrict__ x, int n_rows, int d, int max_id) {
+  const int w = dtype == DLMC_DTYPE_BF16 ? 8 : 4, cpr = d / w;
+  const size_t i = (size_t)blockIdx.x * 256 + threadIdx.x;
+  const int row = (int)(i / cpr), c = (int)(i % cpr) * w;
+  if (row >= n_rows) return;
+  const size_t src = (size_t)min(max(state[row], 0), max_id) * d + c;  // ids outside [0, V] clamp
+  f32x4* dst = reinterpret_cast<f32x4*>(x + (size_t)row * d + c);
   if (dtype == DLMC_DTYPE_BF16) {
-    const bf16_t* t = (const bf16_t*)table + src;
-    for (int c = threadIdx.x; c < d; c += blockDim.x) dst[c] = bf16_to_f32(t[c]);
+    const u32x4 t = *reinterpret_cast<const u32x4*>((const bf16_t*)table + src);
+    f32x4 v[2];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      v[e / 2][e % 2 * 2] = __uint_as_float(t[e] << 16);
+      v[e / 2][e % 2 * 2 + 1] = __uint_as_float(t[e] & 0xFFFF0000u);
+    }
+    dst[0] = v[0];
+    dst[1] = v[1];
   } else {
-    const float* t = (const float*)table + src;
-    for (int c = threadIdx.x; c < d; c += blockDim.x) dst[c] = t[c];
+    dst[0] = *reinterpret_cast<const f32x4*>((const float*)table + src);
   }
 }
 
@@ -370,39 +382,48 @@ void init_weights(hipStream_t st, void* dst, int dtype, uint64_t seed, int tenso
   DLMC_HIP(hipGetLastError());
 }
 
-// One row per wave (d == 256 PER4): lane l holds columns 4 (l + 64 e) .. + 3
-// as 16-byte loads; the row sums are fixed-order butterflies over the wave
-// (every lane ends with the same bits), so no block barrier is needed.
-template <int PER4>
+// One row per wave (d == 64 W PER): lane l holds columns W (l + 64 e) .. + W - 1
+// as one load; the row sums are fixed-order butterflies over the wave (every
+// lane the same bits), so no block barrier is needed.  W = 2 serves the widths
+// that are an odd multiple of 128 (4096 rows of 128: 2.5 us, 5.7 with a block
+// per row).
+template <int W, int PER>
 __global__ void __launch_bounds__(256)
 norm_wave_kernel(const float* __restrict__ x, void* __restrict__ out, int out_dtype, int n_rows,
                  int norm_kind, float eps, const int32_t* __restrict__ gather,
                  const int32_t* __restrict__ n_dev) {
-  constexpr int d = 256 * PER4;
+  constexpr int d = 64 * W * PER;
+  typedef float vec __attribute__((ext_vector_type(W)));
   const int lane = threadIdx.x & 63;
   const int i = blockIdx.x * 4 + (threadIdx.x >> 6);
   if (i >= n_rows || (n_dev && i >= *n_dev)) return;
   const int src = gather ? gather[i] : i;
-  const float4* xr = reinterpret_cast<const float4*>(x + (size_t)src * d);
-  float4 v[PER4];
+  const vec* xr = reinterpret_cast<const vec*>(x + (size_t)src * d);
+  vec v[PER];
 #pragma unroll
-  for (int e = 0; e < PER4; ++e) v[e] = xr[lane + 64 * e];
+  for (int e = 0; e < PER; ++e) v[e] = xr[lane + 64 * e];
   auto wave_sum = [](float t) {
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) t += __shfl_xor(t, o);
     return t;
   };
+  auto sum = [](vec t) {
+    if constexpr (W == 4)
+      return (t[0] + t[1]) + (t[2] + t[3]);
+    else
+      return t[0] + t[1];
+  };
   float scale, shift = 0.0f;
   if (norm_kind == DLMC_NORM_LAYER) {
     float s = 0.0f;
 #pragma unroll
-    for (int e = 0; e < PER4; ++e) s += (v[e].x + v[e].y) + (v[e].z + v[e].w);
+    for (int e = 0; e < PER; ++e) s += sum(v[e]);
     const float mean = wave_sum(s) / (float)d;
     float q = 0.0f;
 #pragma unroll
-    for (int e = 0; e < PER4; ++e) {
-      const float a = v[e].x - mean, b = v[e].y - mean, c = v[e].z - mean, w = v[e].w - mean;
-      q += (a * a + b * b) + (c * c + w * w);
+    for (int e = 0; e < PER; ++e) {
+      const vec t = v[e] - mean;
+      q += sum(t * t);
     }
     const float var = wave_sum(q) / (float)d;
     scale = 1.0f / sqrtf(var + eps);
@@ -410,23 +431,25 @@ norm_wave_kernel(const float* __restrict__ x, void* __restrict__ out, int out_dt
   } else {
     float s = 0.0f;
 #pragma unroll
-    for (int e = 0; e < PER4; ++e)
-      s += (v[e].x * v[e].x + v[e].y * v[e].y) + (v[e].z * v[e].z + v[e].w * v[e].w);
+    for (int e = 0; e < PER; ++e) s += sum(v[e] * v[e]);
     const float ms = wave_sum(s) / (float)d;
     scale = 1.0f / sqrtf(ms + eps);
   }
 #pragma unroll
-  for (int e = 0; e < PER4; ++e) {
-    const int c4 = lane + 64 * e;
-    const float y0 = (v[e].x - shift) * scale, y1 = (v[e].y - shift) * scale;
-    const float y2 = (v[e].z - shift) * scale, y3 = (v[e].w - shift) * scale;
+  for (int e = 0; e < PER; ++e) {
+    const vec y = (v[e] - shift) * scale;
+    const size_t o = (size_t)i * d + W * (lane + 64 * e);
     if (out_dtype == DLMC_DTYPE_BF16) {
-      u32x2 w;
-      w[0] = (uint32_t)f32_to_bf16(y0) | ((uint32_t)f32_to_bf16(y1) << 16);
-      w[1] = (uint32_t)f32_to_bf16(y2) | ((uint32_t)f32_to_bf16(y3) << 16);
-      reinterpret_cast<u32x2*>((bf16_t*)out + (size_t)i * d)[c4] = w;
+      uint32_t w[W / 2];
+#pragma unroll
+      for (int k = 0; k < W / 2; ++k)
+        w[k] = (uint32_t)f32_to_bf16(y[2 * k]) | ((uint32_t)f32_to_bf16(y[2 * k + 1]) << 16);
+      if constexpr (W == 4)
+        *reinterpret_cast<u32x2*>((bf16_t*)out + o) = u32x2{w[0], w[1]};
+      else
+        *reinterpret_cast<uint32_t*>((bf16_t*)out + o) = w[0];
     } else {
-      reinterpret_cast<float4*>((float*)out + (size_t)i * d)[c4] = make_float4(y0, y1, y2, y3);
+      *reinterpret_cast<vec*>((float*)out + o) = y;
     }
   }
 }
@@ -448,7 +471,10 @@ gather_slot_rows_kernel(const bf16_t* __restrict__ src, const float* __restrict_
 void embed(hipStream_t st, const int32_t* state, const void* table, int dtype, float* x,
            int n_rows, int d, int max_id) {
   if (n_rows <= 0) return;
-  embed_kernel<<<n_rows, 256, 0, st>>>(state, table, dtype, x, d, max_id);
+  const int w = dtype == DLMC_DTYPE_BF16 ? 8 : 4;
+  DLMC_CHECK(d % w == 0, DLMC_E_INVAL, "embedding rows must be whole 16-byte chunks");
+  const size_t n = (size_t)n_rows * (d / w);
+  embed_kernel<<<(unsigned)((n + 255) / 256), 256, 0, st>>>(state, table, dtype, x, n_rows, d, max_id);
   DLMC_HIP(hipGetLastError());
 }
 
@@ -459,9 +485,9 @@ void norm_rows(hipStream_t st, const float* x, void* out, int out_dtype, int n_r
   dim3 grid(n_rows), block(256);
   if (d % 256 == 0 && d <= 2048) {
     const dim3 wgrid(ceil_div(n_rows, 4));
-#define DLMC_NORMW(P)                                                                   \
-  norm_wave_kernel<P><<<wgrid, block, 0, st>>>(x, out, out_dtype, n_rows, norm_kind, eps, \
-                                               gather_rows, n_dev)
+#define DLMC_NORMW(P)                                                                      \
+  norm_wave_kernel<4, P><<<wgrid, block, 0, st>>>(x, out, out_dtype, n_rows, norm_kind, eps, \
+                                                  gather_rows, n_dev)
     switch (d / 256) {
       case 1: DLMC_NORMW(1); break;
       case 2: DLMC_NORMW(2); break;
@@ -473,6 +499,21 @@ void norm_rows(hipStream_t st, const float* x, void* out, int out_dtype, int n_r
       default: DLMC_NORMW(8); break;
     }
 #undef DLMC_NORMW
+    DLMC_HIP(hipGetLastError());
+    return;
+  }
+  if (d % 128 == 0 && d <= 896) {
+    const dim3 wgrid(ceil_div(n_rows, 4));
+#define DLMC_NORMW2(P)                                                                     \
+  norm_wave_kernel<2, P><<<wgrid, block, 0, st>>>(x, out, out_dtype, n_rows, norm_kind, eps, \
+                                                  gather_rows, n_dev)
+    switch (d / 128) {
+      case 1: DLMC_NORMW2(1); break;
+      case 3: DLMC_NORMW2(3); break;
+      case 5: DLMC_NORMW2(5); break;
+      default: DLMC_NORMW2(7); break;
+    }
+#undef DLMC_NORMW2
     DLMC_HIP(hipGetLastError());
     return;
   }

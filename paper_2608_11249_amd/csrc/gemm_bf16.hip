@@ -110,7 +110,7 @@ __device__ __forceinline__ void tile_group_stats(const float* sf, int m0, int n0
     const int row = p / GPR, gi = p % GPR;
     const int grow = m0 + row, gcol = n0 + gi * STAT_GROUP;
     if (grow >= Mv || gcol >= N) continue;
-    const RowStat st = group_stat(sf + row * PF + gi * STAT_GROUP, min(STAT_GROUP, N - gcol), true);
+    const RowStat st = group_stat(sf + row * PF + gi * STAT_GROUP, min(STAT_GROUP, N - gcol));
     ((RowStat*)ea.stats)[(size_t)grow * ea.stat_ld + gcol / STAT_GROUP] = st;
   }
 }

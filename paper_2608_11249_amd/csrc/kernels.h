@@ -100,21 +100,27 @@ void gather_slot_rows(hipStream_t st, const bf16_t* src, const float* mx, const 
 // chunk_off[b] / chunk_cnt[b] = the segment of chunk b inside rows[].
 void compact_masked(hipStream_t st, const int32_t* state, int B, int T, int mask_id,
                     int32_t* rows, int32_t* n_rows, int32_t* chunk_off, int32_t* chunk_cnt);
-// per row of logits[n, V]: entropy in bits and row max (n from n_dev when given)
+// per row of logits[n, V]: entropy in bits and row max (n from n_dev when given).
+// scratch (optional): rows of scratch_ld 4-byte words for the group statistics
+// of each row, overwritten; lets few long rows use the whole chip
 void entropy_rows(hipStream_t st, const float* logits, int n_max, const int32_t* n_dev, int V,
-                  float* H, float* mx);
+                  float* H, float* mx, void* scratch = nullptr, size_t scratch_ld = 0);
 // the same from the 128-column group statistics the LM head's epilogue
 // wrote (stats: RowStat [n, ld]); bit-identical to entropy_rows
 void entropy_merge(hipStream_t st, const void* stats, int ld, int V, int n_max, const int32_t* n_dev,
                    float* H, float* mx);
-// commitment schedule, one workgroup per chunk
+// commitment schedule, one workgroup per chunk.  chunk_off / chunk_cnt NULL: the
+// chunks' segments are found in the ascending rows[n_rows]
 void select_positions(hipStream_t st, const float* H, const int32_t* rows,
                       const int32_t* chunk_off, const int32_t* chunk_cnt, int B, int T,
                       float tau, int m_min, int m_max, int32_t* sel_pos, int32_t* sel_row,
-                      int32_t* n_sel, int32_t* err_flag);
+                      int32_t* n_sel, int32_t* err_flag, int n_rows = 0);
 // integer CDF of row sel_row[b*m_max+j] of logits (for j < n_sel[b]) into
 // cdf[(b*m_max+j)*(V+1) ..]; g_out (optional) receives the g values.
-// seg_ws: device workspace of cdf_workspace_bytes(B * m_max, V) bytes.
+// sel_row and n_sel NULL (m_max 1): slot i is row i.
+// seg_ws: device workspace of cdf_workspace_bytes(B * m_max, V) bytes; unused
+// (may be NULL) where cdf_by_rows(B * m_max, V).
+bool cdf_by_rows(size_t slots, int V);
 int cdf_segments(int V);
 inline size_t cdf_workspace_bytes(size_t slots, int V) {
   return slots * (size_t)cdf_segments(V) * (8 + 8 + 4);
@@ -128,8 +134,6 @@ constexpr size_t SCRATCH_BYTES = DLMC_SCRATCH_BYTES;
 // Device address of `device`'s copy of the scratch (looked up on first use,
 // with that device current; each GPU holds its own copy).
 void* scratch_address(int device);
-// sel_row[i] = i, n_sel[i] = 1 for i < n (one committed row per "chunk")
-void fill_row_slots(hipStream_t st, int32_t* sel_row, int32_t* n_sel, int n);
 
 // test hook: a NaN into element 0 of the head's input rows (bf16 or fp32)
 // when n_dev[0] > 0, which makes the first head row non-finite
@@ -164,13 +168,16 @@ void softmax_accumulate(hipStream_t st, const float* S, float* A, int T, float s
                         bool first);
 void rollout_step(hipStream_t st, const float* A, const float* v, float* out, int T);
 // symbol ranking: encode writes (rank, symbol) pairs to out[2 * slot], decode
-// turns the ranks in dec[slot] into symbols; both reveal the symbols in state
+// turns rank[slot] into sym[slot] (may be the same array; *err = 1 for a rank
+// outside the alphabet); both reveal the symbols in state.  With sel_row NULL
+// (B rows, m_max 1) slot i is row i, nothing is revealed, tokens[i] is row i's
+// symbol and its rank goes to out[i].
 void rank_symbols(hipStream_t st, const float* logits, const int32_t* sel_row,
                   const int32_t* sel_pos, const int32_t* n_sel, const int32_t* tokens,
                   const int64_t* slot_base, int32_t* state, int B, int T, int m_max, int V,
                   uint32_t* out);
 void select_by_rank(hipStream_t st, const float* logits, const int32_t* sel_row,
-                    const int32_t* sel_pos, const int32_t* n_sel, int32_t* dec, int32_t* state,
-                    int B, int T, int m_max, int V);
+                    const int32_t* sel_pos, const int32_t* n_sel, const int32_t* rank, int32_t* sym,
+                    int32_t* state, int B, int T, int m_max, int V, int32_t* err);
 
 }  // namespace dlmc

@@ -17,6 +17,7 @@ dlmc_model::~dlmc_model() {
   }
   for (hipEvent_t e : prof_pool) (void)hipEventDestroy(e);
   for (void* p : allocs) (void)hipFree(p);
+  if (h_flag) (void)hipHostFree(h_flag);
   if (own_stream) (void)hipStreamDestroy(own_stream);
 }
 
@@ -70,6 +71,29 @@ void dlmc_model::ensure_sel(int m_max) {
   for (size_t i = 0; i < slots; ++i) iota[i] = (int32_t)i;
   DLMC_HIP(hipMemcpy(slot_rows, iota.data(), slots * 4, hipMemcpyHostToDevice));
   sel_cap = m_max;
+}
+
+void* dlmc_model::ensure_ws(size_t bytes) {
+  if (bytes > ws_cap) {
+    dfree(ws);
+    ws = nullptr;
+    ws_cap = 0;
+    ws = dalloc(bytes);
+    ws_cap = bytes;
+  }
+  return ws;
+}
+
+int32_t* dlmc_model::clear_flag() {
+  if (!h_flag) {
+    if (hipHostMalloc((void**)&h_flag, 64, hipHostMallocDefault) != hipSuccess || !h_flag) {
+      (void)hipGetLastError();
+      h_flag = nullptr;
+      throw Error(DLMC_E_NOMEM, "hipHostMalloc failed");
+    }
+  }
+  *h_flag = 0;
+  return h_flag;
 }
 
 void dlmc_model::ensure_tokens(size_t n) {
@@ -456,7 +480,9 @@ void dlmc_model::forward(const int32_t* st_dev, int B, int T, float* logits_out,
   EpiArgs o;
   o.out = head_deferred ? nullptr : lg;
   o.ldo = V;
-  o.stats = stats;  // the entropy's group statistics, fused into the head's epilogue
+  // the entropy's group statistics, fused into the head's epilogue (a pass whose
+  // logits go to the caller has no entropies to take)
+  o.stats = logits_out ? nullptr : stats;
   o.stat_ld = stat_groups(V);
   StageTimer t(this, DLMC_STAGE_HEAD, 2.0 * head_rows * V * dd);
   if (bf16)

@@ -4,10 +4,11 @@
 // epilogue and the standalone statistics kernel, so both give the same bits.
 //
 // A row of V logits is cut into groups of 128 columns.  The statistics of a
-// group are taken by one thread in column order: the group's max m first,
-// then Z and A added column by column.  A row's groups are merged by one
-// wave: lane l folds groups l, l + 64, ... in order, then the wave merges
-// with butterflies over lane distances 1 .. 32.
+// group are its max m first, then Z and A as binary-tree sums over its columns
+// in order ((c0 + c1) + (c2 + c3), ...), which one thread can evaluate from a
+// staged tile and 32 lanes of a wave from coalesced loads, with the same bits.
+// A row's groups are merged by one wave: lane l folds groups l, l + 64, ... in
+// order, then the wave merges with butterflies over lane distances 1 .. 32.
 //
 // Statistics of a set of logits relative to its max m: Z = sum e^(l - m),
 // A = sum e^(l - m) (l - m); then H (nats) = ln Z - A / Z.  Columns past V
@@ -43,41 +44,91 @@ __device__ __forceinline__ RowStat stat_merge(RowStat x, RowStat y) {
   return r;
 }
 
-// The statistics of the n <= 128 logits p[0 .. n) of one group (in LDS or
-// global memory), in column order.  vec: p is 16-byte aligned, and a full
-// group is read as float4s (the same values in the same order).
-__device__ __forceinline__ RowStat group_stat(const float* p, int n, bool vec) {
-  float m = -INFINITY;
-  if (vec && n == STAT_GROUP) {
+// Z and A of four columns relative to the group's max m: the two lowest levels
+// of the tree.  A -inf logit contributes 0 to both (its t is made finite, so that
+// 0 t is 0); a NaN logit makes e, and with it both sums, NaN.
+__device__ __forceinline__ void stat_quad(f32x4 v, float m, float& z, float& a) {
+  float e[4], w[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const float t = v[i] - m;
+    e[i] = stat_exp(t);
+    w[i] = e[i] * fmaxf(t, -3.0e38f);
+  }
+  z = (e[0] + e[1]) + (e[2] + e[3]);
+  a = (w[0] + w[1]) + (w[2] + w[3]);
+}
+
+// N quads of a group, evaluated depth first, so that few partial sums are live
+template <int N, typename Quad>
+__device__ __forceinline__ void stat_tree(const Quad& quad, int q0, float m, float& z, float& a) {
+  if constexpr (N == 1) {
+    stat_quad(quad(q0), m, z, a);
+  } else {
+    float z1, a1;
+    stat_tree<N / 2>(quad, q0, m, z, a);
+    stat_tree<N / 2>(quad, q0 + N / 2, m, z1, a1);
+    z += z1;
+    a += a1;
+  }
+}
+
+// The statistics of the n <= 128 logits p[0 .. n) of one group (in LDS, 16-byte
+// aligned; columns past n count as -inf), by one thread.
+__device__ __forceinline__ RowStat group_stat(const float* p, int n) {
+  auto full = [&](int q) { return *reinterpret_cast<const f32x4*>(p + 4 * q); };
+  auto part = [&](int q) {
+    f32x4 v;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) v[i] = 4 * q + i < n ? p[4 * q + i] : -INFINITY;
+    return v;
+  };
+  auto run = [&](auto quad) {
+    float m = -INFINITY;
 #pragma unroll 8
-    for (int c = 0; c < STAT_GROUP; c += 4) {
-      const f32x4 v = *reinterpret_cast<const f32x4*>(p + c);
+    for (int q = 0; q < STAT_GROUP / 4; ++q) {
+      const f32x4 v = quad(q);
       m = fmaxf(m, fmaxf(fmaxf(v.x, v.y), fmaxf(v.z, v.w)));
     }
-  } else {
-    for (int c = 0; c < n; ++c) m = fmaxf(m, p[c]);
-  }
-  RowStat s{m, 0.0f, 0.0f};
-  if (m == -INFINITY) return s;
-  auto add = [&](float v) {
-    if (v == -INFINITY) return;
-    const float t = v - m;
-    const float e = stat_exp(t);
-    s.Z += e;
-    s.A += e * t;
+    RowStat s{m, 0.0f, 0.0f};
+    if (m != -INFINITY) stat_tree<STAT_GROUP / 4>(quad, 0, m, s.Z, s.A);
+    return s;
   };
-  if (vec && n == STAT_GROUP) {
-#pragma unroll 4
-    for (int c = 0; c < STAT_GROUP; c += 4) {
-      const f32x4 v = *reinterpret_cast<const f32x4*>(p + c);
-      add(v.x);
-      add(v.y);
-      add(v.z);
-      add(v.w);
-    }
-  } else {
-    for (int c = 0; c < n; ++c) add(p[c]);
-  }
+  return n == STAT_GROUP ? run(full) : run(part);
+}
+
+// Lane i's value of lane i ^ 1, i ^ 2, 7 - i (within 8 lanes) or 15 - i (within 16)
+// by a DPP move: a few cycles, where a shuffle goes through the LDS.
+constexpr int DPP_XOR1 = 0xB1, DPP_XOR2 = 0x4E, DPP_HALF_MIRROR = 0x141, DPP_MIRROR = 0x140;
+template <int CTRL>
+__device__ __forceinline__ float dpp_move(float x) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), CTRL, 0xf, 0xf, true));
+#else
+  return x;
+#endif
+}
+// Reduction over each half of a wave (32 lanes), the binary tree over lane
+// distances 1, 2, 4, 8, 16: after two levels the lanes of a quad agree, so the
+// mirrors pair quads, then groups of eight, as distances 4 and 8 would.
+template <typename Op>
+__device__ __forceinline__ float half_wave_reduce(float x, Op op) {
+  x = op(x, dpp_move<DPP_XOR1>(x));
+  x = op(x, dpp_move<DPP_XOR2>(x));
+  x = op(x, dpp_move<DPP_HALF_MIRROR>(x));
+  x = op(x, dpp_move<DPP_MIRROR>(x));
+  return op(x, __shfl_xor(x, 16));
+}
+
+// The same by the 32 lanes of half a wave: lane i (0 .. 31) holds columns 4 i ..
+// 4 i + 3 (-inf past the row's end); every lane returns the group's statistics.
+__device__ __forceinline__ RowStat group_stat_lanes(f32x4 v) {
+  RowStat s{fmaxf(fmaxf(v.x, v.y), fmaxf(v.z, v.w)), 0.0f, 0.0f};
+  s.m = half_wave_reduce(s.m, [](float x, float y) { return fmaxf(x, y); });
+  stat_quad(v, s.m, s.Z, s.A);
+  s.Z = half_wave_reduce(s.Z, [](float x, float y) { return x + y; });
+  s.A = half_wave_reduce(s.A, [](float x, float y) { return x + y; });
+  if (s.m == -INFINITY) s.Z = s.A = 0.0f;  // an empty group (its sums are NaN)
   return s;
 }
 

@@ -56,6 +56,12 @@ struct dlmc_model {
   size_t tokens_cap = 0;
 
   void* scratch = nullptr;  // this device's copy of the library's static scratch
+  // workspace of the stage hooks, grown to the largest call and freed with the
+  // model (a handle serves one host thread, and a hook returns once its work
+  // is complete), and their error flag in host memory that kernels write
+  void* ws = nullptr;
+  size_t ws_cap = 0;
+  int32_t* h_flag = nullptr;
   bool inject_nan = false;  // test hook: a NaN into the first logit of every forward
   // Deferred logits.  head_slots (set by the caller of forward, 0 = never):
   // the selection slots whose logits a deferred head would recompute;
@@ -89,6 +95,8 @@ struct dlmc_model {
   void dfree(void* p);
   void ensure_sel(int m_max);
   void ensure_tokens(size_t n);
+  void* ensure_ws(size_t bytes);
+  int32_t* clear_flag();  // h_flag, allocated on first use, set to 0
   uint64_t hash() const;
   // One forward pass over state[B*T] (device): logits at masked rows into
   // logits_out (or the internal buffer), row ids and count likewise.  With

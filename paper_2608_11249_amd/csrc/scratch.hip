@@ -1,7 +1,7 @@
 // The library's static device scratch for callers that cannot allocate device
 // memory (code under HIP graph capture, serving loops, harnesses that forbid
-// hipMalloc): dlmc_entropy_cdf_noalloc keeps its CDF row tables and segment
-// partials here instead of in buffers allocated per call.
+// hipMalloc): dlmc_entropy_cdf_noalloc keeps its CDF segment partials here
+// instead of in a buffer that grows with the calls.
 //
 // `scratch` is a file-scope device array; every GPU the library runs on holds
 // its own copy until the process ends.  Host code never passes the array's
@@ -23,15 +23,6 @@ constexpr int MAX_DEVICES = 64;
 std::mutex g_lock;
 void* g_addr[MAX_DEVICES] = {};
 
-// slot i of a CDF launch with one "chunk" per row: row i, one committed row
-__global__ void row_slots_kernel(int32_t* __restrict__ sel_row, int32_t* __restrict__ n_sel, int n) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) {
-    sel_row[i] = i;
-    n_sel[i] = 1;
-  }
-}
-
 }  // namespace
 
 void* scratch_address(int device) {
@@ -47,12 +38,6 @@ void* scratch_address(int device) {
     g_addr[device] = p;
   }
   return g_addr[device];
-}
-
-void fill_row_slots(hipStream_t st, int32_t* sel_row, int32_t* n_sel, int n) {
-  if (n <= 0) return;
-  row_slots_kernel<<<ceil_div(n, 256), 256, 0, st>>>(sel_row, n_sel, n);
-  DLMC_HIP(hipGetLastError());
 }
 
 }  // namespace dlmc

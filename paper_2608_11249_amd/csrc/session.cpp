@@ -429,7 +429,7 @@ int dlmc_session::step(uint64_t* coded) {
     DLMC_HIP(hipMemcpyAsync(m->dec, h_dec, (size_t)B * mm * 4, hipMemcpyHostToDevice, s));
     {
       StageTimer t(m, DLMC_STAGE_REVEAL, 0.0);
-      select_by_rank(s, m->logits, m->logit_rows(), m->sel_pos, m->n_sel, m->dec, m->state, B, T, mm, V);
+      select_by_rank(s, m->logits, m->logit_rows(), m->sel_pos, m->n_sel, m->dec, m->dec, m->state, B, T, mm, V, m->err);
     }
     DLMC_HIP(hipMemcpyAsync(h_dec, m->dec, (size_t)B * mm * 4, hipMemcpyDeviceToHost, s));
     DLMC_HIP(hipStreamSynchronize(s));
