@@ -76,7 +76,7 @@ template <int DH, int QB, int NB>
 __global__ void __launch_bounds__(2 * QB, 256 / QB)
 attn_bf16_kernel(const bf16_t* __restrict__ Q, const bf16_t* __restrict__ Kg,
                  const bf16_t* __restrict__ Vt, bf16_t* __restrict__ O, int H, int T, int Tp,
-                 float scale_log2) {
+                 float scale_log2, float2* __restrict__ ml) {
   constexpr int NWV = QB / 32;       // waves per block (32 queries each)
   constexpr int NS = DH / 16;        // k steps of S^T
   constexpr int RB = DH * 2;         // bytes per K row
@@ -309,6 +309,7 @@ attn_bf16_kernel(const bf16_t* __restrict__ Q, const bf16_t* __restrict__ Kg,
 
   const int q = q0 + lr;
   if (q < T) {
+    if (ml && lg == 0) ml[bh * Tp + q] = make_float2(m_run, l_run);
     const float inv = 1.0f / l_run;
     bf16_t* orow = O + ((size_t)b * T + q) * (size_t)(H * DH) + h * DH;
 #pragma unroll
@@ -345,7 +346,7 @@ template <int DH>
 __global__ void __launch_bounds__(256)
 attn_f32_kernel(const float* __restrict__ Q, const float* __restrict__ Kg,
                 const float* __restrict__ Vt, float* __restrict__ O, int H, int T, int Tp,
-                float scale) {
+                float scale, float2* __restrict__ ml) {
   constexpr int KP = DH + 4, VP = KT + 4, ND = DH / 16;
   __shared__ __attribute__((aligned(16))) float Ks[KT * KP];
   __shared__ __attribute__((aligned(16))) float Vs[DH * VP];
@@ -431,6 +432,7 @@ attn_f32_kernel(const float* __restrict__ Q, const float* __restrict__ Kg,
   l += __shfl_xor(l, 16);
   l += __shfl_xor(l, 32);
   if (q < T) {
+    if (ml && lg == 0) ml[bh * Tp + q] = make_float2(m, l);
     float* orow = O + ((size_t)b * T + q) * (size_t)(H * DH) + h * DH;
 #pragma unroll
     for (int t = 0; t < ND; ++t) {
@@ -445,7 +447,7 @@ attn_f32_kernel(const float* __restrict__ Q, const float* __restrict__ Kg,
 }  // namespace
 
 void attention_bf16(hipStream_t st, const bf16_t* q, const bf16_t* k, const bf16_t* vt,
-                    bf16_t* out, int B, int H, int T, int Tp, int dh) {
+                    bf16_t* out, int B, int H, int T, int Tp, int dh, float2* ml) {
   if (B <= 0 || T <= 0) return;
   DLMC_CHECK(Tp % 128 == 0 && Tp >= T, DLMC_E_INVAL, "attention: padded length must be a multiple of 128");
   DLMC_CHECK(dh == 128 || dh == 64, DLMC_E_INVAL, "bf16 attention supports head dims 64 and 128");
@@ -459,7 +461,7 @@ void attention_bf16(hipStream_t st, const bf16_t* q, const bf16_t* k, const bf16
     // keep two 128-query blocks per CU
     constexpr int NB = QB == 256 ? 3 : 2;
     dim3 grid(ceil_div(T, QB) * H * B), block(2 * QB);
-    attn_bf16_kernel<DH, QB, NB><<<grid, block, 0, st>>>(q, k, vt, out, H, T, Tp, scale_log2);
+    attn_bf16_kernel<DH, QB, NB><<<grid, block, 0, st>>>(q, k, vt, out, H, T, Tp, scale_log2, ml);
   };
   using I64 = std::integral_constant<int, 64>;
   using I128 = std::integral_constant<int, 128>;
@@ -473,16 +475,16 @@ void attention_bf16(hipStream_t st, const bf16_t* q, const bf16_t* k, const bf16
 }
 
 void attention_f32(hipStream_t st, const float* q, const float* k, const float* vt, float* out,
-                   int B, int H, int T, int Tp, int dh) {
+                   int B, int H, int T, int Tp, int dh, float2* ml) {
   if (B <= 0 || T <= 0) return;
   DLMC_CHECK(Tp % 128 == 0 && Tp >= T, DLMC_E_INVAL, "attention: padded length must be a multiple of 128");
   dim3 grid(ceil_div(T, 64), H, B), block(256);
   const float scale = 1.0f / sqrtf((float)dh);
   switch (dh) {
-    case 16: attn_f32_kernel<16><<<grid, block, 0, st>>>(q, k, vt, out, H, T, Tp, scale); break;
-    case 32: attn_f32_kernel<32><<<grid, block, 0, st>>>(q, k, vt, out, H, T, Tp, scale); break;
-    case 64: attn_f32_kernel<64><<<grid, block, 0, st>>>(q, k, vt, out, H, T, Tp, scale); break;
-    case 128: attn_f32_kernel<128><<<grid, block, 0, st>>>(q, k, vt, out, H, T, Tp, scale); break;
+    case 16: attn_f32_kernel<16><<<grid, block, 0, st>>>(q, k, vt, out, H, T, Tp, scale, ml); break;
+    case 32: attn_f32_kernel<32><<<grid, block, 0, st>>>(q, k, vt, out, H, T, Tp, scale, ml); break;
+    case 64: attn_f32_kernel<64><<<grid, block, 0, st>>>(q, k, vt, out, H, T, Tp, scale, ml); break;
+    case 128: attn_f32_kernel<128><<<grid, block, 0, st>>>(q, k, vt, out, H, T, Tp, scale, ml); break;
     default: throw Error(DLMC_E_INVAL, "fp32 attention supports head dims 16, 32, 64, 128");
   }
   DLMC_HIP(hipGetLastError());

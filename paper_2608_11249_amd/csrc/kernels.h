@@ -68,11 +68,13 @@ void swiglu_f32(hipStream_t st, const float* in, float* out, int M, int F);
 
 // ---------------------------------------------------------------- attention
 // Non-causal softmax(Q K^T / sqrt(dh)) V over all T keys of each chunk.
-// out is [B*T, H*dh] row-major.
+// out is [B*T, H*dh] row-major.  ml, if given, takes each row's (m, l) at
+// [b, h, t] with pitch Tp: a probability is e^(s - m) / l of the scaled score s
+// (bf16: 2^(s log2(e) - m) / l).
 void attention_bf16(hipStream_t st, const bf16_t* q, const bf16_t* k, const bf16_t* vt,
-                    bf16_t* out, int B, int H, int T, int Tp, int dh);
+                    bf16_t* out, int B, int H, int T, int Tp, int dh, float2* ml = nullptr);
 void attention_f32(hipStream_t st, const float* q, const float* k, const float* vt, float* out,
-                   int B, int H, int T, int Tp, int dh);
+                   int B, int H, int T, int Tp, int dh, float2* ml = nullptr);
 
 // ---------------------------------------------------------------- elementwise
 // Row layout of an initialised weight tensor inside its device buffer.
@@ -162,11 +164,15 @@ struct DecSlot {
 void decode_symbols(hipStream_t st, const uint32_t* cdf, const int32_t* n_sel, int B, int m_max,
                     int V, int P, int W, bool rans, uint64_t rans_lo, const uint8_t* payload,
                     DecSlot* slots, int32_t* dec, uint32_t* iv, int32_t* err);
-// attention-based context: A[i, :] (+)= w softmax(scale S[i, :]) (rows T,
-// pitch T), and out = (A^T v + v) / 2
-void softmax_accumulate(hipStream_t st, const float* S, float* A, int T, float scale, float w,
-                        bool first);
-void rollout_step(hipStream_t st, const float* A, const float* v, float* out, int T);
+// attention-based context: the head-averaged map A [T, T] (pitch ld, a multiple
+// of 64) of one chunk's Q and K [H, Tp, dh] and attention's (m, l), and the rollout
+// out = v through maps L - 1 .. 0 (each T rows of pitch ld); v has ld entries, ws
+// 2 ROLLOUT_PARTS ld
+constexpr int ROLLOUT_PARTS = 64;
+void attention_map(hipStream_t st, const void* q, const void* k, const float2* ml, float* A, bool bf16,
+                   int H, int T, int Tp, int dh, int ld);
+void rollout(hipStream_t st, const float* maps, int L, const float* v, float* ws, float* out, int T,
+             int ld);
 // symbol ranking: encode writes (rank, symbol) pairs to out[2 * slot], decode
 // turns rank[slot] into sym[slot] (may be the same array; *err = 1 for a rank
 // outside the alphabet); both reveal the symbols in state.  With sel_row NULL

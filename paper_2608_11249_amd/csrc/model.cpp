@@ -358,22 +358,11 @@ void dlmc_model::forward(const int32_t* st_dev, int B, int T, float* logits_out,
   resid.ldo = d;
   const double norm_bytes = Md * dd * (4.0 + es);
   DLMC_CHECK(!attn_maps || B == 1, DLMC_E_INVAL, "attention maps are taken one chunk at a time");
-  // head-averaged attention probabilities of layer l into attn_maps[l] (one
-  // S = Q_h K_h^T product per head, softmax added in head order)
+  // head-averaged attention probabilities of a layer, from its Q, K and row statistics
+  float2* ml = attn_maps ? ctx_ml : nullptr;
   auto attention_map = [&](int l) {
-    float* A = attn_maps + (size_t)l * T * T;
-    const float scale = 1.0f / std::sqrt((float)dh);
-    for (int hd = 0; hd < H; ++hd) {
-      EpiArgs e;
-      e.out = ctx_S;
-      e.ldo = T;
-      const size_t off = (size_t)hd * Tp * dh;
-      if (bf16)
-        gemm_bf16(s, (const bf16_t*)q + off, (const bf16_t*)k + off, T, T, dh, nullptr, EPI_STORE_F32, e);
-      else
-        gemm_f32(s, (const float*)q + off, (const float*)k + off, T, T, dh, nullptr, EPI_STORE_F32, e);
-      softmax_accumulate(s, ctx_S, A, T, scale, 1.0f / H, hd == 0);
-    }
+    const int ld = ctx_pitch(T);
+    dlmc::attention_map(s, q, k, ml, attn_maps + (size_t)l * T * ld, bf16, H, T, Tp, dh, ld);
   };
   int layer_index = 0;
   for (const Layer& w : layers) {
@@ -387,10 +376,13 @@ void dlmc_model::forward(const int32_t* st_dev, int B, int T, float* logits_out,
         StageTimer t(this, DLMC_STAGE_QKV, 2.0 * Md * 3.0 * dd * dd);
         gemm_bf16(s, (const bf16_t*)h, (const bf16_t*)w.wqkv, M, 3 * d, d, nullptr, EPI_QKV_ROPE, qkv);
       }
-      if (attn_maps) attention_map(layer_index);
       {
         StageTimer t(this, DLMC_STAGE_ATTN, 4.0 * B * H * (double)T * T * dh);
-        attention_bf16(s, (const bf16_t*)q, (const bf16_t*)k, (const bf16_t*)vt, (bf16_t*)attn, B, H, T, Tp, dh);
+        attention_bf16(s, (const bf16_t*)q, (const bf16_t*)k, (const bf16_t*)vt, (bf16_t*)attn, B, H, T, Tp, dh, ml);
+      }
+      if (attn_maps) {
+        attention_map(layer_index);
+        if (layer_index + 1 == (int)layers.size()) break;  // nothing reads the rest
       }
       {
         StageTimer t(this, DLMC_STAGE_OPROJ, 2.0 * Md * dd * dd);
@@ -409,10 +401,13 @@ void dlmc_model::forward(const int32_t* st_dev, int B, int T, float* logits_out,
           qkv_rope_f32(s, tmp, M, qkv);
         }
       }
-      if (attn_maps) attention_map(layer_index);
       {
         StageTimer t(this, DLMC_STAGE_ATTN, 4.0 * B * H * (double)T * T * dh);
-        attention_f32(s, (const float*)q, (const float*)k, (const float*)vt, (float*)attn, B, H, T, Tp, dh);
+        attention_f32(s, (const float*)q, (const float*)k, (const float*)vt, (float*)attn, B, H, T, Tp, dh, ml);
+      }
+      if (attn_maps) {
+        attention_map(layer_index);
+        if (layer_index + 1 == (int)layers.size()) break;
       }
       {
         StageTimer t(this, DLMC_STAGE_OPROJ, 2.0 * Md * dd * dd);
@@ -514,39 +509,40 @@ void dlmc_model::row_stats(int n_max) {
 
 void dlmc_model::context_scores(const int32_t* tokens, int T, std::vector<float>& score) {
   DLMC_CHECK(T >= 1 && T <= cfg.max_chunk, DLMC_E_INVAL, "chunk length exceeds the model's workspace");
-  const int L = cfg.n_layers, V = cfg.vocab;
+  const int L = cfg.n_layers, V = cfg.vocab, ld = ctx_pitch(T);
   if (T > ctx_T) {
-    dfree(ctx_maps);
-    dfree(ctx_S);
-    dfree(ctx_v);
-    dfree(ctx_state);
-    ctx_maps = (float*)dalloc((size_t)std::max(L, 1) * T * T * 4);
-    ctx_S = (float*)dalloc((size_t)T * T * 4);
-    ctx_v = (float*)dalloc((size_t)2 * T * 4);
-    ctx_state = (int32_t*)dalloc((size_t)T * 4);
+    for (void* p : {(void*)ctx_maps, (void*)ctx_ml, (void*)ctx_v, (void*)ctx_ws, (void*)ctx_state}) dfree(p);
+    ctx_maps = ctx_v = ctx_ws = nullptr;
+    ctx_ml = nullptr;
+    ctx_state = nullptr;
+    ctx_T = 0;
+    ctx_maps = (float*)dalloc((size_t)std::max(L, 1) * T * ld * 4);
+    ctx_ml = (float2*)dalloc((size_t)cfg.n_heads * round_up(T, 128) * sizeof(float2));
+    ctx_v = (float*)dalloc((size_t)4 * ld * 4);
+    ctx_ws = (float*)dalloc((size_t)2 * ROLLOUT_PARTS * ld * 4);
+    ctx_state = (int32_t*)dalloc((size_t)2 * T * 4);
     ctx_T = T;
   }
-  score.assign(T, 0.0f);
-  std::vector<int32_t> st(T);
-  std::vector<float> v(T);
-  for (int parity = 0; parity < 2; ++parity) {
+  // both passes' states and indicators, then their results, in one copy each
+  std::vector<int32_t> st((size_t)2 * T);
+  std::vector<float> v((size_t)2 * ld, 0.0f);
+  for (int parity = 0; parity < 2; ++parity)
     for (int p = 0; p < T; ++p) {
       const bool masked = (p & 1) == parity;
-      st[p] = masked ? V : tokens[p];
-      v[p] = masked ? 1.0f : 0.0f;
+      st[(size_t)parity * T + p] = masked ? V : tokens[p];
+      v[(size_t)parity * ld + p] = masked ? 1.0f : 0.0f;
     }
-    DLMC_HIP(hipMemcpyAsync(ctx_state, st.data(), (size_t)T * 4, hipMemcpyHostToDevice, stream));
-    DLMC_HIP(hipMemcpyAsync(ctx_v, v.data(), (size_t)T * 4, hipMemcpyHostToDevice, stream));
-    forward(ctx_state, 1, T, nullptr, nullptr, nullptr, -1, false, ctx_maps);
+  DLMC_HIP(hipMemcpyAsync(ctx_state, st.data(), st.size() * 4, hipMemcpyHostToDevice, stream));
+  DLMC_HIP(hipMemcpyAsync(ctx_v, v.data(), v.size() * 4, hipMemcpyHostToDevice, stream));
+  float* res = ctx_v + (size_t)2 * ld;
+  for (int parity = 0; parity < 2; ++parity) {
+    forward(ctx_state + (size_t)parity * T, 1, T, nullptr, nullptr, nullptr, -1, false, ctx_maps);
     // 1_M^T A~_L ... A~_1, last layer first
-    float *in = ctx_v, *out = ctx_v + T;
-    for (int l = L - 1; l >= 0; --l) {
-      rollout_step(stream, ctx_maps + (size_t)l * T * T, in, out, T);
-      std::swap(in, out);
-    }
-    DLMC_HIP(hipMemcpyAsync(v.data(), in, (size_t)T * 4, hipMemcpyDeviceToHost, stream));
-    DLMC_HIP(hipStreamSynchronize(stream));
-    for (int p = 0; p < T; ++p)
-      if ((p & 1) != parity) score[p] = v[p];
+    rollout(stream, ctx_maps, L, ctx_v + (size_t)parity * ld, ctx_ws, res + (size_t)parity * ld, T, ld);
   }
+  DLMC_HIP(hipMemcpyAsync(v.data(), res, v.size() * 4, hipMemcpyDeviceToHost, stream));
+  DLMC_HIP(hipStreamSynchronize(stream));
+  // a position is scored in the pass where it is visible
+  score.resize(T);
+  for (int p = 0; p < T; ++p) score[p] = v[(size_t)((p & 1) ^ 1) * ld + p];
 }

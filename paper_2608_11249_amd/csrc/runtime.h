@@ -106,11 +106,13 @@ struct dlmc_model {
                int32_t* n_rows_out, int64_t rows_hint = -1, bool rows_given = false,
                float* attn_maps = nullptr);
   // attention-based context: per layer head-averaged attention maps of one
-  // chunk (B = 1) written to attn_maps [L, T, T] by forward (the head is then
-  // skipped); context_scores runs the two half-masked passes and returns the
+  // chunk (B = 1) written to attn_maps [L, T, ctx_pitch(T)] by forward (which then
+  // ends with the last map); context_scores runs the two half-masked passes and returns the
   // rollout score of every position (host tokens and scores)
-  float *ctx_maps = nullptr, *ctx_S = nullptr, *ctx_v = nullptr;
+  float *ctx_maps = nullptr, *ctx_v = nullptr, *ctx_ws = nullptr;
+  float2* ctx_ml = nullptr;
   int32_t* ctx_state = nullptr;
+  static int ctx_pitch(int T) { return dlmc::round_up(T, 64); }
   int ctx_T = 0;
   void context_scores(const int32_t* tokens, int T, std::vector<float>& score);
   // entropy (bits) and max of the first n_rows[0] (at most n_max) head rows of
