@@ -317,10 +317,8 @@ attn_bf16_kernel(const bf16_t* __restrict__ Q, const bf16_t* __restrict__ Kg,
 #pragma unroll
       for (int a = 0; a < 4; ++a) {
         const int d = t * 32 + a * 8 + lg * 4;
-        const uint32_t w0 = (uint32_t)f32_to_bf16(o[t][4 * a] * inv) |
-                            ((uint32_t)f32_to_bf16(o[t][4 * a + 1] * inv) << 16);
-        const uint32_t w1 = (uint32_t)f32_to_bf16(o[t][4 * a + 2] * inv) |
-                            ((uint32_t)f32_to_bf16(o[t][4 * a + 3] * inv) << 16);
+        const uint32_t w0 = pack_bf16(o[t][4 * a] * inv, o[t][4 * a + 1] * inv);
+        const uint32_t w1 = pack_bf16(o[t][4 * a + 2] * inv, o[t][4 * a + 3] * inv);
         *reinterpret_cast<u32x2*>(orow + d) = u32x2{w0, w1};
       }
   }

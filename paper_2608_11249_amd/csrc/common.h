@@ -42,11 +42,21 @@ struct Error : std::runtime_error {
 __host__ __device__ inline float bf16_to_f32(bf16_t b) {
   return __builtin_bit_cast(float, (uint32_t)b << 16);
 }
-// round to nearest even (inputs here are never NaN)
+// round to nearest even (inputs here are never NaN); on the device one
+// v_cvt_pk_bf16_f32, which rounds the same way
 __host__ __device__ inline bf16_t f32_to_bf16(float f) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  return __builtin_bit_cast(bf16_t, (__bf16)f);
+#else
   uint32_t u = __builtin_bit_cast(uint32_t, f);
   u += 0x7FFFu + ((u >> 16) & 1u);
   return (bf16_t)(u >> 16);
+#endif
+}
+// the bf16 of a in the low half, of b in the high half
+__device__ __forceinline__ uint32_t pack_bf16(float a, float b) {
+  typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+  return __builtin_bit_cast(uint32_t, bf16x2{(__bf16)a, (__bf16)b});
 }
 
 constexpr int ceil_div(int a, int b) { return (a + b - 1) / b; }

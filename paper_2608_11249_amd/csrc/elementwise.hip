@@ -177,8 +177,8 @@ norm4_kernel(const float* __restrict__ x, void* __restrict__ out, int out_dtype,
     const float y2 = (v[e].z - shift) * scale, y3 = (v[e].w - shift) * scale;
     if (out_dtype == DLMC_DTYPE_BF16) {
       u32x2 w;
-      w[0] = (uint32_t)f32_to_bf16(y0) | ((uint32_t)f32_to_bf16(y1) << 16);
-      w[1] = (uint32_t)f32_to_bf16(y2) | ((uint32_t)f32_to_bf16(y3) << 16);
+      w[0] = pack_bf16(y0, y1);
+      w[1] = pack_bf16(y2, y3);
       reinterpret_cast<u32x2*>((bf16_t*)out + (size_t)i * d)[c4] = w;
     } else {
       reinterpret_cast<float4*>((float*)out + (size_t)i * d)[c4] = make_float4(y0, y1, y2, y3);
@@ -277,7 +277,7 @@ gemm_f32_kernel(const float* __restrict__ A, const float* __restrict__ Bw, int M
       const int row = tid >> 3, p4 = (tid & 7) * 4, hh = p4 / half, p = p4 % half;  // 4 pairs
       const int grow = m0 + row;
       if (grow >= Mv) return;
-      const int b = grow / ea.T, t = grow - b * ea.T, h = (n0 - which * d) / dh + hh;
+      const int b = ea.chunk_of(grow), t = grow - b * ea.T, h = (n0 - which * d) / dh + hh;
       const f32x4 lo = *reinterpret_cast<const f32x4*>(sm + row * P + hh * dh + p);
       const f32x4 hi = *reinterpret_cast<const f32x4*>(sm + row * P + hh * dh + p + half);
       const f32x4 c = *reinterpret_cast<const f32x4*>(ea.rope_cos + t * half + p);
@@ -297,7 +297,7 @@ gemm_f32_kernel(const float* __restrict__ A, const float* __restrict__ Bw, int M
       for (int e = 0; e < 8; ++e) {
         const int grow = m0 + r0 + e;
         if (grow >= Mv) break;
-        const int b = grow / ea.T, t = grow - b * ea.T;
+        const int b = ea.chunk_of(grow), t = grow - b * ea.T;
         ((float*)ea.vt)[(((size_t)b * ea.H + v / dh) * dh + v % dh) * ea.Tp + t] = sm[(r0 + e) * P + col];
       }
     }
@@ -443,7 +443,7 @@ norm_wave_kernel(const float* __restrict__ x, void* __restrict__ out, int out_dt
       uint32_t w[W / 2];
 #pragma unroll
       for (int k = 0; k < W / 2; ++k)
-        w[k] = (uint32_t)f32_to_bf16(y[2 * k]) | ((uint32_t)f32_to_bf16(y[2 * k + 1]) << 16);
+        w[k] = pack_bf16(y[2 * k], y[2 * k + 1]);
       if constexpr (W == 4)
         *reinterpret_cast<u32x2*>((bf16_t*)out + o) = u32x2{w[0], w[1]};
       else

@@ -349,6 +349,7 @@ void dlmc_model::forward(const int32_t* st_dev, int B, int T, float* logits_out,
   qkv.rope_cos = rope_cos;
   qkv.rope_sin = rope_sin;
   qkv.T = T;
+  qkv.inv_T = 1.0f / (float)T;
   qkv.Tp = Tp;
   qkv.H = H;
   qkv.dh = dh;

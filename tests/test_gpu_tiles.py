@@ -58,3 +58,12 @@ def test_few_rows_take_the_ring_tiles():
                          (("gelu64", 65, 24), ("gelu64", 389, 33), ("swiglu128", 257, 40))))
     assert "64x64" in few
     assert many - {"64x64"}
+
+
+@pytest.mark.parametrize("T", [1, 2, 3, 7, 63, 65, 389, 777, 1023, 1024, 4097, 5461, 8191, 8192])
+def test_chunk_of_a_row_by_reciprocal(T):
+    """The rotary epilogue's chunk index, (row + 0.5) * (1 / T) in fp32 rounded
+    down, is row // T for every row a model can have (host only)."""
+    row = np.arange(1 << 20)
+    q = (row.astype(np.float32) + np.float32(0.5)) * (np.float32(1.0) / np.float32(T))
+    assert np.array_equal(q.astype(np.int64), row // T)
