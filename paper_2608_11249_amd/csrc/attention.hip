@@ -165,6 +165,10 @@ attn_bf16_kernel(const bf16_t* __restrict__ Q, const bf16_t* __restrict__ Kg,
   // on most tiles.
   constexpr float RESCALE_LOG2 = 8.0f;
   float m_run = -INFINITY, l_run = 0.0f;
+  // Rows at or beyond T have no say in raising the max: what Q holds there is
+  // left from earlier passes of other lengths, and a chunk's bits must not
+  // depend on it.
+  const bool live = q0 + lr < T;
 
   const int n_kt = (T + KT - 1) / KT;
   const char* ks_base = reinterpret_cast<const char*>(&Ks[0][0]);
@@ -222,7 +226,7 @@ attn_bf16_kernel(const bf16_t* __restrict__ Q, const bf16_t* __restrict__ Kg,
     }
     float mx = fmaxf(fmaxf(m4[0], m4[1]), fmaxf(m4[2], m4[3]));
     mx = fmaxf(mx, __shfl_xor(mx, 32)) * scale_log2;
-    if (__builtin_amdgcn_ballot_w64(mx > m_run + RESCALE_LOG2)) {
+    if (__builtin_amdgcn_ballot_w64(live && mx > m_run + RESCALE_LOG2)) {
       const float m_new = fmaxf(m_run, mx);
       const float alpha = fast_exp2(m_run - m_new);
       l_run *= alpha;
