@@ -170,6 +170,16 @@ struct DecSlot {
 void decode_symbols(hipStream_t st, const uint32_t* cdf, const int32_t* n_sel, int B, int m_max,
                     int V, int P, int W, bool rans, uint64_t rans_lo, const uint8_t* payload,
                     DecSlot* slots, int32_t* dec, uint32_t* iv, int32_t* err);
+// Up to MAX_WORD_COPIES copies of 32-bit words in one launch, between device
+// memory and pinned host memory (visible on the other side as a copy's would be:
+// to the host once the stream is synchronised).
+struct WordCopy {
+  const void* src;
+  void* dst;
+  size_t words;
+};
+constexpr int MAX_WORD_COPIES = 6;
+void copy_words(hipStream_t st, const WordCopy* c, int n);
 // attention-based context: the head-averaged map A [T, T] (pitch ld, a multiple
 // of 64) of one chunk's Q and K [H, Tp, dh] and attention's (m, l), and the rollout
 // out = v through maps L - 1 .. 0 (each T rows of pitch ld); v has ld entries, ws

@@ -357,11 +357,11 @@ int dlmc_session::step(uint64_t* coded) {
       h_nsel_up[b] = u;
     }
     h_nsel_up[B] = r;
-    DLMC_HIP(hipMemcpyAsync(m->rows, h_rows, (size_t)std::max(r, 1) * 4, hipMemcpyHostToDevice, s));
-    DLMC_HIP(hipMemcpyAsync(m->n_rows, h_nsel_up + B, 4, hipMemcpyHostToDevice, s));
-    DLMC_HIP(hipMemcpyAsync(m->sel_pos, h_selpos, (size_t)B * mm * 4, hipMemcpyHostToDevice, s));
-    DLMC_HIP(hipMemcpyAsync(m->sel_row, h_selrow, (size_t)B * mm * 4, hipMemcpyHostToDevice, s));
-    DLMC_HIP(hipMemcpyAsync(m->n_sel, h_nsel_up, (size_t)B * 4, hipMemcpyHostToDevice, s));
+    const size_t slots = (size_t)B * mm;
+    const WordCopy up[] = {{h_rows, m->rows, (size_t)r},         {h_nsel_up + B, m->n_rows, 1},
+                           {h_selpos, m->sel_pos, slots},        {h_selrow, m->sel_row, slots},
+                           {h_nsel_up, m->n_sel, (size_t)B}};
+    copy_words(s, up, 5);
     m->forward(m->state, B, T, nullptr, nullptr, nullptr, r, true);
     {
       // row statistics (the maximum feeds the CDF) at the committed rows only
@@ -387,18 +387,23 @@ int dlmc_session::step(uint64_t* coded) {
       decode_symbols(s, m->cdf, m->n_sel, B, mm, V, P, cp.coder_bits, cp.coder == DLMC_CODER_RANS, RANS_L,
                      d_payload, d_dslot, m->dec, m->sym, m->err);
       reveal(s, m->sel_pos, m->n_sel, m->dec, m->state, B, T, mm);
-      DLMC_HIP(hipMemcpyAsync(h_dec, m->dec, (size_t)B * mm * 4, hipMemcpyDeviceToHost, s));
-      DLMC_HIP(hipMemcpyAsync(h_dslot, d_dslot, (size_t)B * sizeof(DecSlot), hipMemcpyDeviceToHost, s));
     }
   } else if (encode) {
     StageTimer t(m, DLMC_STAGE_REVEAL, 0.0);
     rank_symbols(s, m->logits, m->logit_rows(), m->sel_pos, m->n_sel, m->tokens_dev, m->slot_base,
                  m->state, B, T, mm, V, m->sym);
   }
-  DLMC_HIP(hipMemcpyAsync(h_nsel, m->n_sel, (size_t)B * 4, hipMemcpyDeviceToHost, s));
-  DLMC_HIP(hipMemcpyAsync(h_pos, m->sel_pos, (size_t)B * mm * 4, hipMemcpyDeviceToHost, s));
-  DLMC_HIP(hipMemcpyAsync(h_err, m->err, 4, hipMemcpyDeviceToHost, s));
-  if (encode || !rank) DLMC_HIP(hipMemcpyAsync(h_sym, m->sym, (size_t)B * mm * 8, hipMemcpyDeviceToHost, s));
+  {
+    const size_t slots = (size_t)B * mm;
+    WordCopy down[MAX_WORD_COPIES] = {{m->n_sel, h_nsel, (size_t)B}, {m->sel_pos, h_pos, slots}, {m->err, h_err, 1}};
+    int n = 3;
+    if (encode || !rank) down[n++] = {m->sym, h_sym, 2 * slots};
+    if (!encode && !rank) {
+      down[n++] = {m->dec, h_dec, slots};
+      down[n++] = {d_dslot, h_dslot, (size_t)B * (sizeof(DecSlot) / 4)};
+    }
+    copy_words(s, down, n);
+  }
   DLMC_HIP(hipStreamSynchronize(s));
   if (*h_err == 2) throw Error(DLMC_E_CORRUPT, "decoder target out of range");
   if (*h_err) throw Error(DLMC_E_NUMERIC, "non-finite entropy (non-finite logits)");
