@@ -156,8 +156,11 @@ dlmc_status dlmc_model_create(const dlmc_model_config* cfg, uint64_t seed, int32
                               dlmc_model** out);
 /* Free the model and all its device memory.  NULL is ignored. */
 void dlmc_model_destroy(dlmc_model* model);
-/* Use `hip_stream` (a hipStream_t, e.g. torch.cuda.current_stream().cuda_stream)
- * for all device work of this model; NULL selects the library's own stream. */
+/* Use `hip_stream` (a hipStream_t) for all device work of this model;
+ * DLMC_DEFAULT_STREAM selects the device's default stream (handle 0, e.g. torch's
+ * unless another is current), and NULL the library's own stream, which waits
+ * for no other: device memory handed to a call on it has to be ready. */
+#define DLMC_DEFAULT_STREAM ((void*)1)
 dlmc_status dlmc_set_stream(dlmc_model* model, void* hip_stream);
 
 /* ---- compression ------------------------------------------------------- */

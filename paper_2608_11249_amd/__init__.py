@@ -27,6 +27,7 @@ FLAG_CRC = 1
 STAGES = ["embed", "norm", "qkv", "attn", "oproj", "ffn_in", "ffn_out", "head", "entropy",
           "select", "cdf", "reveal", "compact"]
 PROFILE_ONE_LAYER = 1 << 31  # DLMC_PROFILE_ONE_LAYER
+DEFAULT_STREAM = 1  # DLMC_DEFAULT_STREAM
 
 
 class LibraryMissing(RuntimeError):
@@ -342,6 +343,20 @@ class Model:
         _check(lib().dlmc_set_stream(self.handle, stream_handle))
 
     # ---- stage hooks on torch device tensors
+    def _on_current_stream(self, device, fn, *args):
+        """One call on torch's current stream, so that it follows the work that
+        fills its tensors (which live until it returns).  The default stream's
+        handle is 0, for which the library would take its own stream; it has
+        that one back afterwards."""
+        import torch
+        stream = torch.cuda.current_stream(device).cuda_stream
+        self.set_stream(stream or DEFAULT_STREAM)
+        try:
+            _check(fn(self.handle, *(_ptr(a) if torch.is_tensor(a) else a for a in args)))
+        finally:
+            if not stream:
+                self.set_stream(None)
+
     def forward_logits(self, state):
         """state: int32 cuda tensor [B, T].  Returns (logits [n, V], rows [n])."""
         import torch
@@ -350,9 +365,8 @@ class Model:
         logits = torch.empty(B * T * V, dtype=torch.float32, device=state.device)
         rows = torch.empty(B * T, dtype=torch.int32, device=state.device)
         n = torch.zeros(1, dtype=torch.int32, device=state.device)
-        self.set_stream(torch.cuda.current_stream(state.device).cuda_stream)
-        _check(lib().dlmc_forward_logits(self.handle, _ptr(state.contiguous()), B, T, _ptr(logits),
-                                         _ptr(rows), _ptr(n)))
+        self._on_current_stream(state.device, lib().dlmc_forward_logits, state.contiguous(), B, T,
+                                logits, rows, n)
         k = int(n.item())
         return logits[: k * V].view(k, V), rows[:k]
 
@@ -367,9 +381,8 @@ class Model:
         if want_cdf:
             g = torch.empty(n * V, dtype=torch.int32, device=dev)
             cdf = torch.empty(n * (V + 1), dtype=torch.int32, device=dev)
-        self.set_stream(torch.cuda.current_stream(dev).cuda_stream)
-        _check(lib().dlmc_entropy_cdf(self.handle, _ptr(logits.contiguous()), n, cdf_bits, _ptr(H),
-                                      _ptr(mx), _ptr(g), _ptr(cdf)))
+        self._on_current_stream(dev, lib().dlmc_entropy_cdf, logits.contiguous(), n, cdf_bits, H,
+                                mx, g, cdf)
         if want_cdf:
             g, cdf = g.view(n, V), cdf.view(n, V + 1)
         return H, mx, g, cdf
@@ -387,9 +400,8 @@ class Model:
         if want_cdf:
             g = torch.empty(n * V, dtype=torch.int32, device=dev)
             cdf = torch.empty(n * (V + 1), dtype=torch.int32, device=dev)
-        self.set_stream(torch.cuda.current_stream(dev).cuda_stream)
-        _check(lib().dlmc_entropy_cdf_noalloc(self.handle, _ptr(logits.contiguous()), n, cdf_bits,
-                                              _ptr(H), _ptr(mx), _ptr(g), _ptr(cdf)))
+        self._on_current_stream(dev, lib().dlmc_entropy_cdf_noalloc, logits.contiguous(), n,
+                                cdf_bits, H, mx, g, cdf)
         if want_cdf:
             g, cdf = g.view(n, V), cdf.view(n, V + 1)
         return H, mx, g, cdf
@@ -406,9 +418,8 @@ class Model:
         import torch
         n = int(sym.shape[0])
         out = torch.empty(n, dtype=torch.int32, device=logits.device)
-        self.set_stream(torch.cuda.current_stream(logits.device).cuda_stream)
-        _check(lib().dlmc_rank_rows(self.handle, _ptr(logits.contiguous()), n,
-                                    _ptr(sym.contiguous()), _ptr(out)))
+        self._on_current_stream(logits.device, lib().dlmc_rank_rows, logits.contiguous(), n,
+                                sym.contiguous(), out)
         return out
 
     def select_rank_rows(self, logits, rank):
@@ -416,10 +427,10 @@ class Model:
         import torch
         n = int(rank.shape[0])
         out = torch.empty(n, dtype=torch.int32, device=logits.device)
-        self.set_stream(torch.cuda.current_stream(logits.device).cuda_stream)
-        _check(lib().dlmc_select_rank_rows(self.handle, _ptr(logits.contiguous()), n,
-                                           _ptr(rank.contiguous()), _ptr(out)))
+        self._on_current_stream(logits.device, lib().dlmc_select_rank_rows, logits.contiguous(), n,
+                                rank.contiguous(), out)
         return out
+
     def select(self, H, rows, B: int, T: int, tau: float, m_min: int, m_max: int):
         """Schedule on device entropies; returns (sel_pos [B, m_max], sel_row, n_sel [B])."""
         import torch
@@ -427,10 +438,9 @@ class Model:
         sel_pos = torch.full((B, m_max), -1, dtype=torch.int32, device=dev)
         sel_row = torch.full((B, m_max), -1, dtype=torch.int32, device=dev)
         n_sel = torch.zeros(B, dtype=torch.int32, device=dev)
-        self.set_stream(torch.cuda.current_stream(dev).cuda_stream)
-        _check(lib().dlmc_select(self.handle, _ptr(H.contiguous()), _ptr(rows.contiguous()),
-                                 int(rows.numel()), B, T, tau, m_min, m_max, _ptr(sel_pos),
-                                 _ptr(sel_row), _ptr(n_sel)))
+        self._on_current_stream(dev, lib().dlmc_select, H.contiguous(), rows.contiguous(),
+                                int(rows.numel()), B, T, tau, m_min, m_max, sel_pos, sel_row,
+                                n_sel)
         return sel_pos, sel_row, n_sel
 
     def weight(self, tensor_id: int, rows: int, cols: int) -> np.ndarray:

@@ -77,7 +77,9 @@ dlmc_status dlmc_set_stream(dlmc_model* m, void* hip_stream) {
   return guard([&] {
     use(m);
     DLMC_HIP(hipStreamSynchronize(m->stream));
-    m->stream = hip_stream ? (hipStream_t)hip_stream : m->own_stream;
+    m->stream = hip_stream == DLMC_DEFAULT_STREAM ? nullptr
+                : hip_stream                       ? (hipStream_t)hip_stream
+                                                   : m->own_stream;
   });
 }
 

@@ -10,7 +10,7 @@ using namespace dlmc;
 
 dlmc_model::~dlmc_model() {
   if (device >= 0) (void)hipSetDevice(device);
-  if (stream) (void)hipStreamSynchronize(stream);
+  if (own_stream) (void)hipStreamSynchronize(stream);  // stream: NULL for the default stream
   for (auto& r : prof_recs) {
     (void)hipEventDestroy(r.a);
     (void)hipEventDestroy(r.b);
