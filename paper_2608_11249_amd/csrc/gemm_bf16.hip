@@ -108,7 +108,7 @@ __device__ __forceinline__ float rot_hi(float lo, float hi, float c, float s) {
 // first row and column are m0 and n0; one thread per (row, group), the
 // group folded in column order from LDS.
 template <int R, int BN, int PF, int NT>
-__device__ __forceinline__ void tile_group_stats(const float* sf, int m0, int n0, int tid, int Mv,
+__device__ __forceinline__ void tile_group_stats(float* sf, int m0, int n0, int tid, int Mv,
                                                  int N, const EpiArgs& ea) {
   constexpr int GPR = BN / STAT_GROUP;
   static_assert(BN % STAT_GROUP == 0, "whole groups per tile");
