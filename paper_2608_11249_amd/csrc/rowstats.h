@@ -12,7 +12,8 @@
 //
 // Statistics of a set of logits relative to its max m: Z = sum e^(l - m),
 // A = sum e^(l - m) (l - m); then H (nats) = ln Z - A / Z.  Columns past V
-// and -inf logits carry nothing.
+// and -inf logits carry nothing.  A NaN logit makes its group's Z and A NaN, and
+// with them the row's entropy, also in a group with nothing above -inf.
 #pragma once
 
 #include "common.h"
@@ -59,6 +60,12 @@ __device__ __forceinline__ void stat_quad(f32x4 v, float m, float& z, float& a) 
   a = (w[0] + w[1]) + (w[2] + w[3]);
 }
 
+// NaN if one of four columns is, else 0
+__device__ __forceinline__ float stat_quad_nan(f32x4 v) {
+  const bool nan = v.x != v.x || v.y != v.y || v.z != v.z || v.w != v.w;
+  return nan ? __builtin_nanf("") : 0.0f;
+}
+
 // N quads of a group, evaluated depth first, so that few partial sums are live
 template <int N, typename Quad>
 __device__ __forceinline__ void stat_tree(const Quad& quad, int q0, float m, float& z, float& a) {
@@ -90,7 +97,12 @@ __device__ __forceinline__ RowStat group_stat(float* p, int n) {
     m = fmaxf(m, fmaxf(fmaxf(v.x, v.y), fmaxf(v.z, v.w)));
   }
   RowStat s{m, 0.0f, 0.0f};
-  if (m != -INFINITY) stat_tree<STAT_GROUP / 4>(quad, 0, m, s.Z, s.A);
+  if (m != -INFINITY) {
+    stat_tree<STAT_GROUP / 4>(quad, 0, m, s.Z, s.A);
+  } else {  // the max passes over NaN: an empty group, unless it holds one
+#pragma unroll 1
+    for (int q = 0; q < STAT_GROUP / 4; ++q) s.Z = s.A = s.Z + stat_quad_nan(quad(q));
+  }
   return s;
 }
 
@@ -125,7 +137,10 @@ __device__ __forceinline__ RowStat group_stat_lanes(f32x4 v) {
   stat_quad(v, s.m, s.Z, s.A);
   s.Z = half_wave_reduce(s.Z, [](float x, float y) { return x + y; });
   s.A = half_wave_reduce(s.A, [](float x, float y) { return x + y; });
-  if (s.m == -INFINITY) s.Z = s.A = 0.0f;  // an empty group (its sums are NaN)
+  if (!(s.m > -INFINITY)) {  // nothing above -inf: an empty group, unless it holds a NaN
+    s.m = -INFINITY;
+    s.Z = s.A = half_wave_reduce(stat_quad_nan(v), [](float x, float y) { return x + y; });
+  }
   return s;
 }
 

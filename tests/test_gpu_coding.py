@@ -75,6 +75,31 @@ def test_cdf_rows_exact_from_g(V, n, P, scale):
         assert np.array_equal(cdf[i].view(np.uint32).astype(np.int64), want)
 
 
+@pytest.mark.parametrize("V", [129, 257, 300, 8193, 8320])
+def test_a_nan_makes_its_rows_entropy_nan(V):
+    """Wherever the NaN is -- alone in the last group of 128 columns, all of a
+    group, among -inf -- and in every form of the statistics; a group of -inf
+    alone carries nothing."""
+    log("nan rows", V)
+    g0 = (V - 1) // 128 * 128                            # the last group
+    n = 6
+    lg = wl.random_logits(V, n, V, 2.0)
+    lg[1, g0:] = np.nan
+    lg[2, :128] = np.nan
+    lg[3, g0:] = -np.inf
+    lg[3, V - 1] = np.nan
+    lg[4, g0:] = -np.inf
+    lg[4, 0] = 1.0
+    dev = torch.from_numpy(lg).cuda()
+    with handle(V) as m:
+        forms = [m.entropy_cdf(dev, 24, want_cdf=c)[0].cpu().numpy() for c in (True, False)]
+        forms.append(m.entropy_cdf_noalloc(dev, 24)[0].cpu().numpy())
+        many = m.entropy_cdf(dev.repeat(50, 1), 24)[0].cpu().numpy()
+    for H in forms:
+        assert np.array_equal(H, many[:n], equal_nan=True)
+        assert np.isnan(H[1:4]).all() and np.isfinite(H[[0, 4, 5]]).all()
+
+
 @pytest.mark.parametrize("V", [2, 63, 1025, 32768, 40000])
 def test_rank_rows_forms(V):
     log("rank", V)
