@@ -10,10 +10,14 @@
 // the bin that holds rank r is found from the counts, and the few candidates in
 // it are collected and ranked exactly by (key, id): three coalesced reads of
 // the row, and counting that spreads over the bins.  Rows that this cannot
-// split -- non-finite logits, more than CAP candidates in the bin -- take a radix
-// selection over the keys instead (four 8-bit digit passes with LDS histograms,
-// whose leading digits most logits share, then a prefix count in id order);
-// 512 rows of 32768 by it alone take 193 us.
+// split -- non-finite logits, more than CAP candidates in the bin (one logit far
+// from the others leaves those in a few bins) -- take a radix selection over the
+// keys: 11 bits a pass, as many counts as bins, until no more than CAP keys match,
+// and where more are equal, a prefix count in id order.  A call over 512 rows of
+// 32768 takes 58 us by bins and, by radix as well, 103 (an infinity in each row),
+// 152 (a logit of 1e4) to 256 us (all equal), where four 8-bit passes and the count
+// alone took 248, 261 and 465, and behind the bins 206, 225 and 417; 64 rows of
+// 126464 with a logit of 1e4 take 200 us, against 332 alone and 373 behind the bins.
 // Both kernels also reveal the symbol in the state.
 #include "kernels.h"
 
@@ -108,39 +112,78 @@ rank_kernel(RankArgs a, const int32_t* __restrict__ tokens, const int64_t* __res
   }
 }
 
-constexpr int BINS = 2048, CAP = 2048;
+// CAP: comparing n candidates with one another takes n^2 / 128 LDS reads, which 2048
+// of them made dearer than another pass over a row (512 rows of 4099, two values
+// in a bin each: 162 us a call, 83 with 1280)
+constexpr int BINS = 2048, CAP = 1280;
 
 // bin of a logit of a row with maximum hi (monotone in l: larger logits first)
 __device__ __forceinline__ int rank_bin(float l, float hi, float scale) {
   return min((int)((hi - l) * scale), BINS - 1);
 }
 
+// The bin (count) that holds rank r: sh[0] = the bin, sh[1] = the rank inside it,
+// sh[3] = its count.
+__device__ __forceinline__ void pick_bin(const uint32_t* hist, uint32_t r, uint32_t* lds, uint32_t* sh) {
+  static_assert(BINS == 2 * RT, "two bins per thread");
+  const uint32_t h0 = hist[2 * threadIdx.x], h1 = hist[2 * threadIdx.x + 1];
+  uint32_t total;
+  const uint32_t base = block_exclusive_scan(h0 + h1, lds, &total);
+  if (r >= base && r < base + h0 + h1) {
+    const int second = r >= base + h0;
+    sh[0] = 2 * threadIdx.x + second;
+    sh[1] = r - base - (second ? h0 : 0u);
+    sh[3] = second ? h1 : h0;
+  }
+  __syncthreads();
+}
+
+// *found = the id of the candidate of rank r among n candidates (key, id); cand has
+// one more entry, all ones, if n is odd
+__device__ __forceinline__ void rank_candidates(const uint64_t* cand, int n, uint32_t r, int32_t* found) {
+  for (int i = threadIdx.x; i < n; i += RT) {
+    const uint64_t me = cand[i];
+    uint32_t before = 0;
+#pragma unroll 4
+    for (int k = 0; k < n; k += 2) {
+      const ulonglong2 c = *reinterpret_cast<const ulonglong2*>(cand + k);
+      before += (c.x < me) + (c.y < me);
+    }
+    if (before == r) *found = (int32_t)(uint32_t)me;
+  }
+}
+
 // the general selection: see the head of the file
 __device__ void radix_select(const float* __restrict__ row, int V, uint32_t rest, uint32_t* hist,
-                             uint32_t* lds, uint32_t* sh, int32_t* found) {
+                             uint64_t* cand, uint32_t* lds, uint32_t* sh, int32_t* found) {
   uint32_t prefix = 0, mask = 0;
-  for (int shift = 24; shift >= 0; shift -= 8) {
-    for (int d = threadIdx.x; d < 256; d += RT) hist[d] = 0;
+#pragma unroll 1
+  for (int shift = 21; shift >= 0; shift -= shift > 10 ? 11 : shift > 0 ? shift : 1) {
+    const uint32_t digit = shift > 0 ? 2047u : 1023u;  // bits 21 .. 31, 10 .. 20, 0 .. 9
+    for (int d = threadIdx.x; d < BINS; d += RT) hist[d] = 0;
+    if (threadIdx.x == 0) sh[2] = 0;
     __syncthreads();
+#pragma unroll 8
     for (int v = threadIdx.x; v < V; v += RT) {
       const uint32_t k = rank_key(row[v]);
-      if ((k & mask) == prefix) atomicAdd(&hist[(k >> shift) & 255u], 1u);
+      if ((k & mask) == prefix) atomicAdd(&hist[(k >> shift) & digit], 1u);
     }
     __syncthreads();
-    if (threadIdx.x == 0) {
-      uint32_t cum = 0, d = 0;
-      for (; d < 255; ++d) {
-        if (cum + hist[d] > rest) break;
-        cum += hist[d];
-      }
-      sh[0] = prefix | (d << shift);
-      sh[1] = rest - cum;
-    }
-    __syncthreads();
-    prefix = sh[0];
+    pick_bin(hist, rest, lds, sh);
+    prefix |= sh[0] << shift;
     rest = sh[1];
-    mask |= 255u << shift;
-    __syncthreads();
+    mask |= digit << shift;
+    if (sh[3] <= (uint32_t)CAP) {
+      if (threadIdx.x == 0) cand[sh[3]] = ~0ull;
+#pragma unroll 8
+      for (int v = threadIdx.x; v < V; v += RT) {
+        const uint32_t k = rank_key(row[v]);
+        if ((k & mask) == prefix) cand[atomicAdd(&sh[2], 1u)] = (uint64_t)k << 32 | (uint32_t)v;
+      }
+      __syncthreads();
+      rank_candidates(cand, (int)sh[2], rest, found);
+      return;
+    }
   }
   // the rest-th id (in id order) among the symbols whose key is `prefix`
   const int per = (V + RT - 1) / RT, lo = threadIdx.x * per, hi = min(lo + per, V);
@@ -165,10 +208,10 @@ __device__ void radix_select(const float* __restrict__ row, int V, uint32_t rest
 __global__ void __launch_bounds__(RT)
 select_rank_kernel(RankArgs a, const int32_t* rank, int32_t* sym, int32_t* err) {
   __shared__ uint32_t hist[BINS];
-  __shared__ uint64_t cand[CAP];
+  __shared__ __attribute__((aligned(16))) uint64_t cand[CAP + 2];
   __shared__ uint32_t lds[RT / 64 + 1];
   __shared__ float red[2][RT / 64];
-  __shared__ uint32_t sh[4];  // bin, rank inside it, candidates
+  __shared__ uint32_t sh[4];  // bin, rank inside it, candidates, their count
   __shared__ int32_t found;
   int slot;
   const float* row;
@@ -213,21 +256,11 @@ select_rank_kernel(RankArgs a, const int32_t* rank, int32_t* sym, int32_t* err) 
 #pragma unroll 8
     for (int v = tid; v < V; v += RT) atomicAdd(&hist[rank_bin(row[v], mx, scale)], 1u);
     __syncthreads();
-    const uint32_t h0 = hist[2 * tid], h1 = hist[2 * tid + 1];
-    static_assert(BINS == 2 * RT, "two bins per thread");
-    uint32_t total;
-    const uint32_t base = block_exclusive_scan(h0 + h1, lds, &total);
-    const uint32_t r = (uint32_t)want;
-    if (r >= base && r < base + h0 + h1) {
-      const int second = r >= base + h0;
-      sh[0] = 2 * tid + second;
-      sh[1] = r - base - (second ? h0 : 0u);
-      sh[3] = second ? h1 : h0;
-    }
-    __syncthreads();
+    pick_bin(hist, (uint32_t)want, lds, sh);
     const int bin = (int)sh[0];
     general = sh[3] > (uint32_t)CAP;
     if (!general) {
+      if (tid == 0) cand[sh[3]] = ~0ull;
 #pragma unroll 8
       for (int v = tid; v < V; v += RT) {
         const float l = row[v];
@@ -235,16 +268,10 @@ select_rank_kernel(RankArgs a, const int32_t* rank, int32_t* sym, int32_t* err) 
           cand[atomicAdd(&sh[2], 1u)] = (uint64_t)rank_key(l) << 32 | (uint32_t)v;
       }
       __syncthreads();
-      const int n = (int)sh[2];
-      for (int i = tid; i < n; i += RT) {
-        const uint64_t me = cand[i];
-        uint32_t before = 0;
-        for (int k = 0; k < n; ++k) before += cand[k] < me;
-        if (before == sh[1]) found = (int32_t)(uint32_t)me;
-      }
+      rank_candidates(cand, (int)sh[2], sh[1], &found);
     }
   }
-  if (general) radix_select(row, V, (uint32_t)want, hist, lds, sh, &found);
+  if (general) radix_select(row, V, (uint32_t)want, hist, cand, lds, sh, &found);
   __syncthreads();
   if (tid == 0) {
     sym[slot] = found;

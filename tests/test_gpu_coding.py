@@ -104,7 +104,8 @@ def test_a_nan_makes_its_rows_entropy_nan(V):
 def test_rank_rows_forms(V):
     log("rank", V)
     rng = np.random.default_rng(V)
-    lg = rng.normal(0, 3, (9, V)).astype(np.float32)
+    n = 15
+    lg = rng.normal(0, 3, (n, V)).astype(np.float32)
     lg[1] = 0.5                                          # one value: no bins
     lg[2] = np.round(lg[2])                              # ties, more than fit the candidate list
     lg[3, V // 2] = -np.inf
@@ -114,17 +115,25 @@ def test_rank_rows_forms(V):
     lg[6] = 3.0e38 * np.sign(lg[6])                      # the range overflows
     lg[7, 0] = 1e4                                       # all others in one bin
     lg[8] *= 1e-42                                       # denormals
+    lg[9, V - 1] = -1e4                                  # the same from below
+    lg[10, ::2] = -np.inf
+    lg[11] = np.exp(4 * lg[11])                          # over 60 octaves
+    lg[12] = np.round(lg[12])
+    lg[12, 0] = 1e6                                      # few values, all in one bin
+    lg[13] = -np.inf
+    lg[14, V // 3:] = 1.0 + 2.0 ** -20 * (np.arange(V - V // 3) % 7)  # apart in the last key bits
+    lg[14, 0] = 1e6
     order = np.argsort(-(lg + 0.0).astype(np.float64), axis=1, kind="stable")
     with handle(V) as m:
         dev = torch.from_numpy(lg).cuda()
         for r in sorted({0, 1, V // 3, V // 2, V - 2, V - 1}):
-            rank = torch.full((9,), r, dtype=torch.int32, device="cuda")
+            rank = torch.full((n,), r, dtype=torch.int32, device="cuda")
             sym = m.select_rank_rows(dev, rank)
             assert np.array_equal(sym.cpu().numpy(), order[:, r]), r
             assert np.array_equal(m.rank_rows(dev, sym).cpu().numpy(), rank.cpu().numpy()), r
         for bad in (-1, V):
             with pytest.raises(dl.DlmcError) as e:
-                m.select_rank_rows(dev, torch.full((9,), bad, dtype=torch.int32, device="cuda"))
+                m.select_rank_rows(dev, torch.full((n,), bad, dtype=torch.int32, device="cuda"))
             assert e.value.code == -1
 
 
