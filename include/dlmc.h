@@ -331,8 +331,8 @@ dlmc_status dlmc_select(dlmc_model* model, const float* entropy_bits, const int3
                         int32_t m_max, int32_t* sel_pos, int32_t* sel_row, int32_t* n_sel);
 /* Symbol ranking on device logits[n_rows * vocab] (Definition of Symbol
  * Ranking; equal probabilities ordered by token id): rank[i] of sym[i] in row
- * i, and the inverse, sym[i] of rank[i] (0 <= rank < vocab; device int32
- * arrays of n_rows, n_rows <= 65535). */
+ * i, and the inverse, sym[i] of rank[i] (0 <= rank < vocab, else E_INVAL and
+ * sym is left as it was; device int32 arrays of n_rows, n_rows <= 65535). */
 dlmc_status dlmc_rank_rows(dlmc_model* model, const float* logits, int32_t n_rows,
                            const int32_t* sym, int32_t* rank);
 dlmc_status dlmc_select_rank_rows(dlmc_model* model, const float* logits, int32_t n_rows,

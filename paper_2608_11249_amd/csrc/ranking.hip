@@ -203,10 +203,26 @@ __device__ void radix_select(const float* __restrict__ row, int V, uint32_t rest
   }
 }
 
-// rank[slot] -> sym[slot] (the two may be the same array).  A rank outside the
-// alphabet sets *err and leaves its row alone.
+// *bad = whether one of n ranks lies outside the alphabet, and then *err = 1 (one
+// block; about 3 us of a call)
 __global__ void __launch_bounds__(RT)
-select_rank_kernel(RankArgs a, const int32_t* rank, int32_t* sym, int32_t* err) {
+check_ranks_kernel(const int32_t* __restrict__ rank, int n, int V, int32_t* __restrict__ bad,
+                   int32_t* __restrict__ err) {
+  bool out = false;
+#pragma unroll 4
+  for (int i = threadIdx.x; i < n; i += RT) out |= rank[i] < 0 || rank[i] >= V;
+  out = __syncthreads_or(out);
+  if (threadIdx.x == 0) {
+    *bad = out;
+    if (out) *err = 1;
+  }
+}
+
+// rank[slot] -> sym[slot] (the two may be the same array); nothing where *refuse.
+// A rank outside the alphabet sets *err and leaves its row alone.
+__global__ void __launch_bounds__(RT)
+select_rank_kernel(RankArgs a, const int32_t* rank, int32_t* sym, int32_t* err,
+                   const int32_t* __restrict__ refuse) {
   __shared__ uint32_t hist[BINS];
   __shared__ __attribute__((aligned(16))) uint64_t cand[CAP + 2];
   __shared__ uint32_t lds[RT / 64 + 1];
@@ -215,7 +231,7 @@ select_rank_kernel(RankArgs a, const int32_t* rank, int32_t* sym, int32_t* err) 
   __shared__ int32_t found;
   int slot;
   const float* row;
-  if (!rank_slot(a, slot, row)) return;
+  if ((refuse && *refuse) || !rank_slot(a, slot, row)) return;
   const int V = a.V, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int32_t want = rank[slot];
   if (want < 0 || want >= V) {
@@ -292,13 +308,18 @@ void rank_symbols(hipStream_t st, const float* logits, const int32_t* sel_row,
   DLMC_HIP(hipGetLastError());
 }
 
+void check_ranks(hipStream_t st, const int32_t* rank, int n, int V, int32_t* bad, int32_t* err) {
+  check_ranks_kernel<<<1, RT, 0, st>>>(rank, n, V, bad, err);
+  DLMC_HIP(hipGetLastError());
+}
+
 void select_by_rank(hipStream_t st, const float* logits, const int32_t* sel_row,
                     const int32_t* sel_pos, const int32_t* n_sel, const int32_t* rank, int32_t* sym,
-                    int32_t* state, int B, int T, int m_max, int V, int32_t* err) {
+                    int32_t* state, int B, int T, int m_max, int V, int32_t* err, const int32_t* refuse) {
   if (B <= 0 || m_max <= 0) return;
   DLMC_CHECK(m_max <= 65535 && B <= 65535, DLMC_E_INVAL, "too many rank rows per launch");
   const RankArgs a{logits, sel_row, sel_pos, n_sel, T, m_max, V, state};
-  select_rank_kernel<<<B * m_max, RT, 0, st>>>(a, rank, sym, err);
+  select_rank_kernel<<<B * m_max, RT, 0, st>>>(a, rank, sym, err, refuse);
   DLMC_HIP(hipGetLastError());
 }
 

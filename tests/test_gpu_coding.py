@@ -137,6 +137,28 @@ def test_rank_rows_forms(V):
             assert e.value.code == -1
 
 
+@pytest.mark.parametrize("n,bad", [(1, 0), (9, 8), (1024, 0), (1025, 1024), (5000, 4321)])
+def test_a_rank_outside_the_alphabet_leaves_the_symbols_alone(n, bad):
+    log("bad rank", n, bad)
+    V = 67
+    lg = torch.from_numpy(wl.random_logits(n, n, V, 2.0)).cuda()
+    good = torch.arange(n, dtype=torch.int32, device="cuda") % V
+    call = dl.lib().dlmc_select_rank_rows
+    with handle(V) as m:
+        want = m.select_rank_rows(lg, good)
+        for wrong in (-1, V, 2 ** 31 - 1):
+            rank = good.clone()
+            rank[bad] = wrong
+            sym = torch.full_like(rank, -7)
+            torch.cuda.synchronize()
+            assert call(m.handle, lg.data_ptr(), n, rank.data_ptr(), sym.data_ptr()) == -1
+            assert (sym == -7).all()
+        sym = good.clone()                               # in place
+        torch.cuda.synchronize()
+        assert call(m.handle, lg.data_ptr(), n, sym.data_ptr(), sym.data_ptr()) == 0
+        assert torch.equal(sym, want)
+
+
 @pytest.mark.parametrize("B,T", [(1, 1), (1, 63), (3, 65), (5, 1000), (64, 1024), (40, 1700), (9, 8192)])
 def test_compaction_spans(B, T):
     """Masked rows of a forward pass, over one and several 65536-position spans."""
