@@ -432,10 +432,8 @@ dlmc_status dlmc_select_rank_rows(dlmc_model* m, const float* logits, int32_t n_
     DLMC_CHECK(logits && sym && rank, DLMC_E_INVAL, "NULL argument");
     hipStream_t s = m->stream;
     int32_t* flag = m->clear_flag();
-    // every rank is checked before the first symbol is written
-    check_ranks(s, rank, n_rows, m->cfg.vocab, m->bad_ranks, flag);
     select_by_rank(s, logits, nullptr, nullptr, nullptr, rank, sym, nullptr, n_rows, 1, 1, m->cfg.vocab,
-                   flag, m->bad_ranks);
+                   flag);
     DLMC_HIP(hipStreamSynchronize(s));
     DLMC_CHECK(*(volatile int32_t*)flag == 0, DLMC_E_INVAL, "rank outside the alphabet");
   });

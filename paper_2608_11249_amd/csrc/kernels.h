@@ -193,17 +193,14 @@ void rollout(hipStream_t st, const float* maps, int L, const float* v, float* ws
 // turns rank[slot] into sym[slot] (may be the same array; *err = 1 for a rank
 // outside the alphabet); both reveal the symbols in state.  With sel_row NULL
 // (B rows, m_max 1) slot i is row i, nothing is revealed, tokens[i] is row i's
-// symbol and its rank goes to out[i].  check_ranks sets the device word *bad to
-// whether a rank lies outside the alphabet (then *err = 1); select_by_rank writes
-// nothing if *refuse (optional) is set.
+// symbol and its rank goes to out[i]; a rank outside the alphabet (*err, 0 before the
+// call) then leaves all of sym alone.
 void rank_symbols(hipStream_t st, const float* logits, const int32_t* sel_row,
                   const int32_t* sel_pos, const int32_t* n_sel, const int32_t* tokens,
                   const int64_t* slot_base, int32_t* state, int B, int T, int m_max, int V,
                   uint32_t* out);
 void select_by_rank(hipStream_t st, const float* logits, const int32_t* sel_row,
                     const int32_t* sel_pos, const int32_t* n_sel, const int32_t* rank, int32_t* sym,
-                    int32_t* state, int B, int T, int m_max, int V, int32_t* err,
-                    const int32_t* refuse = nullptr);
-void check_ranks(hipStream_t st, const int32_t* rank, int n, int V, int32_t* bad, int32_t* err);
+                    int32_t* state, int B, int T, int m_max, int V, int32_t* err);
 
 }  // namespace dlmc

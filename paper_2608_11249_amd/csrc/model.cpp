@@ -260,7 +260,6 @@ void create_model(dlmc_model* m, const dlmc_model_config& cfg, uint64_t seed, in
   m->chunk_cnt = (int32_t*)m->dalloc((size_t)cfg.max_batch * 4);
   m->state = (int32_t*)m->dalloc(R * 4);
   m->err = (int32_t*)m->dalloc(4);
-  m->bad_ranks = (int32_t*)m->dalloc(4);
 
   // Q, K, V^T padding rows are read (with zero weight) by attention: keep them finite
   DLMC_HIP(hipMemsetAsync(m->q, 0, qkv_elems * m->esz, st));

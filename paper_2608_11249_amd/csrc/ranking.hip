@@ -14,10 +14,10 @@
 // from the others leaves those in a few bins) -- take a radix selection over the
 // keys: 11 bits a pass, as many counts as bins, until no more than CAP keys match,
 // and where more are equal, a prefix count in id order.  A call over 512 rows of
-// 32768 takes 58 us by bins and, by radix as well, 103 (an infinity in each row),
-// 152 (a logit of 1e4) to 256 us (all equal), where four 8-bit passes and the count
+// 32768 takes 54 us by bins and, by radix as well, 99 (an infinity in each row),
+// 148 (a logit of 1e4) to 253 us (all equal), where four 8-bit passes and the count
 // alone took 248, 261 and 465, and behind the bins 206, 225 and 417; 64 rows of
-// 126464 with a logit of 1e4 take 200 us, against 332 alone and 373 behind the bins.
+// 126464 with a logit of 1e4 take 194 us, against 332 alone and 373 behind the bins.
 // Both kernels also reveal the symbol in the state.
 #include "kernels.h"
 
@@ -114,7 +114,7 @@ rank_kernel(RankArgs a, const int32_t* __restrict__ tokens, const int64_t* __res
 
 // CAP: comparing n candidates with one another takes n^2 / 128 LDS reads, which 2048
 // of them made dearer than another pass over a row (512 rows of 4099, two values
-// in a bin each: 162 us a call, 83 with 1280)
+// in a bin each: 158 us a call, 79 with 1280)
 constexpr int BINS = 2048, CAP = 1280;
 
 // bin of a logit of a row with maximum hi (monotone in l: larger logits first)
@@ -203,30 +203,27 @@ __device__ void radix_select(const float* __restrict__ row, int V, uint32_t rest
   }
 }
 
-// *bad = whether one of n ranks lies outside the alphabet, and then *err = 1 (one
-// block; about 3 us of a call)
+// *err = 1 if one of n ranks lies outside the alphabet (one block)
 __global__ void __launch_bounds__(RT)
-check_ranks_kernel(const int32_t* __restrict__ rank, int n, int V, int32_t* __restrict__ bad,
-                   int32_t* __restrict__ err) {
+check_ranks_kernel(const int32_t* __restrict__ rank, int n, int V, int32_t* __restrict__ err) {
   bool out = false;
 #pragma unroll 4
   for (int i = threadIdx.x; i < n; i += RT) out |= rank[i] < 0 || rank[i] >= V;
-  out = __syncthreads_or(out);
-  if (threadIdx.x == 0) {
-    *bad = out;
-    if (out) *err = 1;
-  }
+  if (__syncthreads_or(out) && threadIdx.x == 0) *err = 1;
 }
 
-// rank[slot] -> sym[slot] (the two may be the same array); nothing where *refuse.
-// A rank outside the alphabet sets *err and leaves its row alone.
+// rank[slot] -> sym[slot] (the two may be the same array).  A rank outside the
+// alphabet sets *err and leaves its row alone, or, with n_check, every row: each
+// block looks at all of rank[0 .. n_check), where another may have put a symbol, in
+// the alphabet like the rank it stands for.  Nothing is done if *refuse is set.
 __global__ void __launch_bounds__(RT)
-select_rank_kernel(RankArgs a, const int32_t* rank, int32_t* sym, int32_t* err,
-                   const int32_t* __restrict__ refuse) {
+select_rank_kernel(RankArgs a, const int32_t* rank, int32_t* sym, int32_t* err, int n_check,
+                   const int32_t* refuse) {
   __shared__ uint32_t hist[BINS];
   __shared__ __attribute__((aligned(16))) uint64_t cand[CAP + 2];
   __shared__ uint32_t lds[RT / 64 + 1];
   __shared__ float red[2][RT / 64];
+  __shared__ int wave_out[RT / 64];
   __shared__ uint32_t sh[4];  // bin, rank inside it, candidates, their count
   __shared__ int32_t found;
   int slot;
@@ -234,10 +231,8 @@ select_rank_kernel(RankArgs a, const int32_t* rank, int32_t* sym, int32_t* err,
   if ((refuse && *refuse) || !rank_slot(a, slot, row)) return;
   const int V = a.V, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int32_t want = rank[slot];
-  if (want < 0 || want >= V) {
-    if (tid == 0) *err = 1;
-    return;
-  }
+  bool out = want < 0 || want >= V;
+  for (int i = tid; i < n_check; i += RT) out |= rank[i] < 0 || rank[i] >= V;
   float mx = -INFINITY, mn = INFINITY;
   bool odd = false;  // a NaN or an infinity
 #pragma unroll 8
@@ -252,9 +247,11 @@ select_rank_kernel(RankArgs a, const int32_t* rank, int32_t* sym, int32_t* err,
     mx = fmaxf(mx, __shfl_xor(mx, o));
     mn = fminf(mn, __shfl_xor(mn, o));
   }
+  out = __any(out);
   if (lane == 0) {
     red[0][wave] = mx;
     red[1][wave] = mn;
+    wave_out[wave] = out;
   }
   for (int d = tid; d < BINS; d += RT) hist[d] = 0;
   if (tid == 0) sh[2] = 0;
@@ -263,6 +260,11 @@ select_rank_kernel(RankArgs a, const int32_t* rank, int32_t* sym, int32_t* err,
   for (int w = 0; w < RT / 64; ++w) {
     mx = fmaxf(mx, red[0][w]);
     mn = fminf(mn, red[1][w]);
+    out |= wave_out[w] != 0;
+  }
+  if (out) {
+    if (tid == 0) *err = 1;
+    return;
   }
   // (BINS - 1/2 of the range: rounding cannot push the minimum past the last bin
   // by more than the clamp takes back)
@@ -308,18 +310,18 @@ void rank_symbols(hipStream_t st, const float* logits, const int32_t* sel_row,
   DLMC_HIP(hipGetLastError());
 }
 
-void check_ranks(hipStream_t st, const int32_t* rank, int n, int V, int32_t* bad, int32_t* err) {
-  check_ranks_kernel<<<1, RT, 0, st>>>(rank, n, V, bad, err);
-  DLMC_HIP(hipGetLastError());
-}
-
 void select_by_rank(hipStream_t st, const float* logits, const int32_t* sel_row,
                     const int32_t* sel_pos, const int32_t* n_sel, const int32_t* rank, int32_t* sym,
-                    int32_t* state, int B, int T, int m_max, int V, int32_t* err, const int32_t* refuse) {
+                    int32_t* state, int B, int T, int m_max, int V, int32_t* err) {
   if (B <= 0 || m_max <= 0) return;
   DLMC_CHECK(m_max <= 65535 && B <= 65535, DLMC_E_INVAL, "too many rank rows per launch");
   const RankArgs a{logits, sel_row, sel_pos, n_sel, T, m_max, V, state};
-  select_rank_kernel<<<B * m_max, RT, 0, st>>>(a, rank, sym, err, refuse);
+  // Without slots a bad rank refuses the call.  Every block checks up to 4096 ranks,
+  // four a thread, behind its other loads; a launch of its own before that took 5 us.
+  const int n = sel_row ? 0 : B;
+  const bool apart = n > 4096;
+  if (apart) check_ranks_kernel<<<1, RT, 0, st>>>(rank, n, V, err);
+  select_rank_kernel<<<B * m_max, RT, 0, st>>>(a, rank, sym, err, apart ? 0 : n, apart ? err : nullptr);
   DLMC_HIP(hipGetLastError());
 }
 

@@ -62,7 +62,6 @@ struct dlmc_model {
   void* ws = nullptr;
   size_t ws_cap = 0;
   int32_t* h_flag = nullptr;
-  int32_t* bad_ranks = nullptr;  // device word of check_ranks
   bool inject_nan = false;  // test hook: a NaN into the first logit of every forward
   // Deferred logits.  head_slots (set by the caller of forward, 0 = never):
   // the selection slots whose logits a deferred head would recompute;
