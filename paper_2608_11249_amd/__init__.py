@@ -180,6 +180,7 @@ class Encoder:
         self._tok = np.ascontiguousarray(tokens, dtype=np.int32)
         self._cp = codec_params(codec, batch, crc)
         h = vp()
+        model._off_default_stream()
         _check(lib().dlmc_encoder_begin(model.handle, ctypes.byref(self._cp), _ptr(self._tok),
                                         len(self._tok), ctypes.byref(h)))
         self.handle = h
@@ -188,6 +189,7 @@ class Encoder:
 
     def step(self) -> bool:
         done, coded = i32(0), u64(0)
+        self.model._off_default_stream()
         _check(lib().dlmc_encoder_step(self.handle, ctypes.byref(done), ctypes.byref(coded)))
         self.coded += coded.value
         self.done = bool(done.value)
@@ -197,6 +199,7 @@ class Encoder:
         bound = self.model.encode_bound(self._cp, len(self._tok))
         out = np.empty(bound, dtype=np.uint8)
         n = u64(0)
+        self.model._off_default_stream()
         _check(lib().dlmc_encoder_finish(self.handle, _ptr(out), bound, ctypes.byref(n)))
         return out[: n.value].tobytes()
 
@@ -222,6 +225,8 @@ class Model:
         _check(lib().dlmc_model_create(ctypes.byref(self.cfg), shape.seed, device, ctypes.byref(h)))
         self.handle = h
         self._trace_cb = None
+        self._stream = None  # what set_stream was last given
+        self._hook_stream = False  # whether that was a stage hook's default stream
 
     def close(self):
         if getattr(self, "handle", None):
@@ -252,6 +257,7 @@ class Model:
         bound = self.encode_bound(cp, len(tok))
         out = np.empty(max(bound, 1), dtype=np.uint8)
         n = u64(0)
+        self._off_default_stream()
         _check(lib().dlmc_encode(self.handle, ctypes.byref(cp), _ptr(tok), len(tok), _ptr(out),
                                  bound, ctypes.byref(n)))
         return out[: n.value].tobytes()
@@ -266,6 +272,7 @@ class Model:
                                              n_chunks, ctypes.byref(bound)))
         out = np.empty(max(bound.value, 1), dtype=np.uint8)
         n = u64(0)
+        self._off_default_stream()
         _check(lib().dlmc_encode_range(self.handle, ctypes.byref(cp), _ptr(tok), len(tok),
                                        first_chunk, n_chunks, _ptr(out), bound.value,
                                        ctypes.byref(n)))
@@ -284,6 +291,7 @@ class Model:
         n = decode_size(data)
         out = np.empty(max(n, 1), dtype=np.int32)
         got = u64(0)
+        self._off_default_stream()
         _check(lib().dlmc_decode(self.handle, _ptr(buf), len(buf), batch, _ptr(out), n,
                                  ctypes.byref(got)))
         return out[: got.value]
@@ -341,21 +349,26 @@ class Model:
 
     def set_stream(self, stream_handle: Optional[int]):
         _check(lib().dlmc_set_stream(self.handle, stream_handle))
+        self._stream = stream_handle or None
+        self._hook_stream = False
+
+    def _off_default_stream(self):
+        """Calls without tensors run on the library's own stream again after a
+        stage hook on the default one."""
+        if self._hook_stream:
+            self.set_stream(None)
 
     # ---- stage hooks on torch device tensors
     def _on_current_stream(self, device, fn, *args):
         """One call on torch's current stream, so that it follows the work that
         fills its tensors (which live until it returns).  The default stream's
-        handle is 0, for which the library would take its own stream; it has
-        that one back afterwards."""
+        handle is 0, for which the library would take its own stream."""
         import torch
-        stream = torch.cuda.current_stream(device).cuda_stream
-        self.set_stream(stream or DEFAULT_STREAM)
-        try:
-            _check(fn(self.handle, *(_ptr(a) if torch.is_tensor(a) else a for a in args)))
-        finally:
-            if not stream:
-                self.set_stream(None)
+        stream = torch.cuda.current_stream(device).cuda_stream or DEFAULT_STREAM
+        if stream != self._stream:
+            self.set_stream(stream)
+            self._hook_stream = stream == DEFAULT_STREAM
+        _check(fn(self.handle, *(_ptr(a) if torch.is_tensor(a) else a for a in args)))
 
     def forward_logits(self, state):
         """state: int32 cuda tensor [B, T].  Returns (logits [n, V], rows [n])."""
@@ -410,6 +423,7 @@ class Model:
         """Attention-based context score of every position of one chunk."""
         t = np.ascontiguousarray(tokens, dtype=np.int32)
         out = np.empty(len(t), dtype=np.float32)
+        self._off_default_stream()
         _check(lib().dlmc_context_scores(self.handle, _ptr(t), len(t), _ptr(out)))
         return out
 

@@ -55,6 +55,11 @@ def test_hooks_wait_for_their_inputs(hook, side):
             got = HOOKS[hook](m, late)
             torch.cuda.synchronize()
         assert all(torch.equal(a, b.cpu()) for a, b in zip(want, got))
-        # a call without tensors afterwards, on the stream the model is left with
+        # calls without tensors afterwards leave the default stream, hooks come back to it
         toks = wl.markov1_tokens(64, V, 1).astype(np.int32)
-        assert np.array_equal(m.context_scores(toks), m.context_scores(toks))
+        scores = m.context_scores(toks)
+        again = HOOKS[hook](m, ready)
+        assert all(torch.equal(a, b.cpu()) for a, b in zip(want, again))
+        assert np.array_equal(scores, m.context_scores(toks))
+        m.set_stream(dl.DEFAULT_STREAM)
+        assert np.array_equal(scores, m.context_scores(toks))
