@@ -382,7 +382,6 @@ struct CdfArgs {
   const int32_t* sel_row;
   const int32_t* n_sel;
   int m_max, V, P, S;
-  float inv_m_max;
   uint32_t* cdf;
   uint32_t* g_out;
   uint64_t* segG;
@@ -400,14 +399,13 @@ __device__ __forceinline__ bool cdf_live(const CdfArgs& c, int slot) {
 // committed row.  A chunk's committed rows are its first few slots, m_max apart:
 // with m_max a multiple of the 8 XCDs the rows of all chunks ran on one of them.
 // There each run of 8 slots is turned round by its chunk's number (64 chunks, one
-// row of 32768 each, m_max 32: 182 -> 28 us; 25 with the j-th slots of all chunks
+// row of 32768 each, m_max 32: 182 -> 30 us; 25 with the j-th slots of all chunks
 // one after another, which made launches with every slot live 4 to 8% slower).
 __device__ __forceinline__ bool cdf_block_slot(const CdfArgs& c, int i, int& slot) {
   slot = i;
-  if (!c.n_sel) return true;
-  // i / m_max, exact below 2^16 as EpiArgs::chunk_of; a run lies in one chunk
-  const int b = __builtin_amdgcn_readfirstlane((int)(((float)i + 0.5f) * c.inv_m_max));
-  if ((c.m_max & 7) == 0) slot = (i & ~7) | ((i + b) & 7);
+  if (!c.n_sel || (c.m_max & 7)) return cdf_live(c, i);
+  const int b = i / c.m_max;  // a run lies in one chunk
+  slot = (i & ~7) | ((i + b) & 7);
   return slot - b * c.m_max < c.n_sel[b];
 }
 __device__ __forceinline__ int cdf_row_of(const CdfArgs& c, int slot) {
@@ -849,7 +847,7 @@ int cdf_segments(int V) { return ceil_div(V, CDF_SEG); }
 // 512 rows of 32768 with g: 61 us by rows, 122 in segments with a 64-bit division
 // per entry; 64 rows of 126464 in segments: 43 us (59).  How many slots hold a
 // committed row is known on the device only.  With up to 64 of 32768 entries, rows
-// take 23 to 32 us however many slots there are; segments 16 to 35 up to 1024 slots,
+// take 23 to 36 us however many slots there are; segments 16 to 35 up to 1024 slots,
 // 25 to 43 at 2048 and 46 to 60 at 4096, most of it for blocks without a row.
 bool cdf_by_rows(size_t slots, int V) { return V <= 32768 && (slots >= 128 || V <= CDF_SEG); }
 
@@ -865,7 +863,6 @@ void cdf_rows(hipStream_t st, const float* logits, const float* mx, const int32_
   c.sel_row = sel_row;
   c.n_sel = n_sel;
   c.m_max = m_max;
-  c.inv_m_max = 1.0f / (float)m_max;
   c.V = V;
   c.P = P;
   c.S = cdf_segments(V);

@@ -1292,7 +1292,7 @@ GemmTiles gemm_bf16_tiles(int M, int N, int K, EpiKind epi, int d, int rows_hint
   // 12288, M = 65536).
   const double c0s_w128 =
       epi == EPI_RESIDUAL ? c0_w128[ei] * std::min(1.0, std::sqrt(768.0 / (double)K))
-      : epi == EPI_QKV_ROPE ? 6.0  // 10.9 for a launch's only wave, 3072 rows at K = 768
+      : epi == EPI_QKV_ROPE ? 6.0  // the first wave's 10.9 is that of K = 768 (3072 rows)
                             : -1.0;
   const double t128 = t_of(128, 128, 512, c0_128[ei], 1.13, N);
   // 192 x 128: QKV tiles must lie inside Q, K or V (d % 128 == 0 holds)
@@ -1303,12 +1303,21 @@ GemmTiles gemm_bf16_tiles(int M, int N, int K, EpiKind epi, int d, int rows_hint
   // a QKV tile must lie inside one of Q, K, V: 256-wide tiles need d % 256 == 0
   const bool wide_ok = epi != EPI_QKV_ROPE || d % 256 == 0;
   if (N % 128 == 0) {
-    auto t_split = [&](int c1) {
-      // with few 256 x 128 tiles a k-tile takes less than with every CU busy
-      const double busy = std::min(1.0, ceil_div(live, 256) * (double)((N - c1) / 128) / 256.0);
-      return t_of(256, 256, 256, c0_w256[ei], 1.53, c1) +
-             t_of(256, 128, 256, c0_w128[ei], 0.62 + 0.36 * busy * busy, N - c1, c0s_w128);
+    // 256 x 128 tiles: with idle CUs a k-tile takes less than with every CU busy, in
+    // a launch's only wave and, starting behind a full one, less so in the last of
+    // several (768 x 3072 at 16384 rows, a wave and a half: 89 us, 114 if the last
+    // counted in full, which chose 128 x 64 tiles at 95).  A QKV launch's fixed cost
+    // falls with K (12288 x 4096 at 300 rows 57 us, 64 with that of K = 768, which
+    // chose 64 x 64 tiles at 62).
+    const double c0_w = c0_w128[ei] * (epi == EPI_QKV_ROPE ? std::min(1.0, std::pow(768.0 / (double)K, 0.6)) : 1.0);
+    auto t_w128 = [&](int cols) {
+      if (cols <= 0) return 0.0;
+      const long tiles = (long)ceil_div(live, 256) * (cols / 128), waves = (tiles + 255) / 256;
+      const double fill = (double)(tiles - (waves - 1) * 256) / 256.0, idle = waves == 1 ? 0.62 : 0.87;
+      return ((double)(waves - 1) * 0.98 + idle + (0.98 - idle) * fill * fill) * nk + c0_w +
+             (double)(waves - 1) * (c0s_w128 >= 0.0 ? c0s_w128 : c0_w);
     };
+    auto t_split = [&](int c1) { return t_of(256, 256, 256, c0_w256[ei], 1.53, c1) + t_w128(N - c1); };
     // one tile shape (all 256 x 128, or all 256 x 256), then a split if it
     // is more than 3% faster (the estimate rounds each part up to whole
     // waves on its own, a margin for the split's tiles that share a wave)
@@ -1336,11 +1345,13 @@ GemmTiles gemm_bf16_tiles(int M, int N, int K, EpiKind epi, int d, int rows_hint
     best = {GEMM_TILES_192x128, 0, 0};
     t_best = t192;
   }
-  // The ring kernel: tiles that share a CU share its LDS, which bounds them, so
-  // its time goes by the tiles per CU (256 CUs), not by waves of slots; fitted to
-  // 64 .. 16384 rows of the small model and 64 .. 3072 of the 8B shape (within
-  // 8% rms for the multi-block shapes, 15% for the one-block ones).  A launch
-  // of at most one tile per CU takes the deep ring (with less LDS per block the
+  // The ring kernel: tiles that share a CU share its LDS, so its time goes by the
+  // tiles per CU (256 CUs), not by waves of slots; fitted to 64 .. 16384 rows of the
+  // small model and 64 .. 3072 of the 8B shape (within 8% rms for the multi-block
+  // shapes, 15% for the one-block ones).  Over 292 launches, 64 .. 65536 rows of the
+  // one and 17 .. 8192 of the other, weights from memory, the whole choice takes 0.6%
+  // more than the fastest form on average and 15% at most (24576 x 4096, 513 rows).
+  // A launch of at most one tile per CU takes the deep ring (with less LDS per block the
   // others run two or three blocks per CU: 15.0 against 12.5 us for 192 tiles
   // of 64 x 64 at K = 3072, but 10.6 against 11.4 us for 576 at K = 768).
   struct RingShape {
