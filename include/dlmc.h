@@ -285,8 +285,8 @@ dlmc_status dlmc_test_head_logits(dlmc_model* model, int32_t mode);
  * epilogue's model width, else unused).  *kind: 0 128 x 128 tiles, 1
  * 192 x 128 tiles (two blocks per CU), 2 the 4-wave kernel with columns
  * [0, *split) on 256 x 256 tiles and [*split, N) on 256 x 128 tiles, 3 64 x 64,
- * 4 128 x 64 and 5 128 x 128 tiles (launches with few tiles).  The
- * choice never changes a result; the GEMMs run in the forward pass of
+ * 4 128 x 64 (both: *split 1 with more LDS stages and one block per CU, else 0)
+ * and 5 128 x 128 tiles (launches with few tiles).  The choice never changes a result; the GEMMs run in the forward pass of
  * Definition 3.  E_INVAL for sizes the GEMM does not take (K % 64 != 0,
  * M, N < 1, paired epilogues with N % 128 != 0) or a NULL output. */
 dlmc_status dlmc_test_gemm_tiles(int32_t M, int32_t N, int32_t K, int32_t epi, int32_t d_model,

@@ -470,8 +470,8 @@ GEMM_EPI = {"store": 0, "residual": 1, "qkv": 2, "gelu": 3, "swiglu": 4}
 
 def gemm_tiles(M: int, N: int, K: int, epi: str, d_model: int = 0):
     """(kind, split) the bf16 GEMM chooses (host only): kind "128x128",
-    "192x128", "4wave" with columns [0, split) on 256 x 256 tiles, "64x64",
-    "128x64" or "128x128deep"."""
+    "192x128", "4wave" with columns [0, split) on 256 x 256 tiles, "64x64" or
+    "128x64" (split: 1 with the deeper ring) or "128x128deep"."""
     kind, split = ctypes.c_int32(), ctypes.c_int32()
     _check(lib().dlmc_test_gemm_tiles(M, N, K, GEMM_EPI[epi], d_model, ctypes.byref(kind),
                                       ctypes.byref(split)))

@@ -235,7 +235,7 @@ dlmc_status dlmc_test_gemm_tiles(int32_t M, int32_t N, int32_t K, int32_t epi, i
                "paired epilogue needs N % 128 == 0");
     const GemmTiles t = gemm_bf16_tiles(M, N, K, (EpiKind)epi, d_model, -1);
     *kind = t.kind;
-    *split = t.split;
+    *split = t.kind == GEMM_TILES_64x64 || t.kind == GEMM_TILES_128x64 ? t.deep : t.split;
   });
 }
 

@@ -334,6 +334,15 @@ TILE_CASES = [
     ((65536, 2304, 768, "qkv", 768), ("192x128", 0)),
     ((65536, 3072, 768, "gelu", 768), ("192x128", 0)),
     ((65536, 32768, 768, "store", 768), ("4wave", 32768)),
+    # launches with few tiles, timed with weights from memory (us, next best form):
+    # the small model on one chunk of 1024, and on 16
+    ((1024, 768, 768, "residual", 768), ("64x64", 1)),            # 5.8, 128x64 7.3
+    ((1024, 2304, 768, "qkv", 768), ("64x64", 0)),                # 10.4, 128x64 10.9
+    ((16384, 768, 3072, "residual", 768), ("4wave", 0)),          # 89, 128x64 95
+    # the 8B shape on an input's last chunk
+    ((100, 12288, 4096, "qkv", 4096), ("128x64", 1)),             # 27, 64x64 32
+    ((300, 12288, 4096, "qkv", 4096), ("4wave", 0)),              # 57, 64x64 62
+    ((777, 4096, 4096, "residual", 4096), ("128x128deep", 0)),     # 33, 128x64 38
 ]
 
 
