@@ -72,7 +72,9 @@ __device__ __forceinline__ bool tile_coords(int bid, int n_tm, int n_tn, int bm,
 // into the constants, and one expression serves both signs: 19 issue slots a
 // value, against 26 with a branch-free select of the two (largest error over
 // [-12, 12] 3.3e-7, against 4.2e-7; 32768 x 3072 x 768 on 192 x 128 tiles 222 ->
-// 203 us, on 256 x 256 tiles 260 -> 205).
+// 203 us, on 256 x 256 tiles 260 -> 205).  For finite v: rows of a norm of up to
+// 8192 columns times weights below 2^8 keep |v| under 3e6 (an infinity would come
+// out as NaN, which the entropies report like an infinity).
 __device__ __forceinline__ float gelu_erf(float v) {
   const float x = fabsf(v);
   const float t = __builtin_amdgcn_rcpf(fmaf(0.3275911f * 0.70710678118654752440f, x, 1.0f));
@@ -106,7 +108,7 @@ __device__ __forceinline__ float rot_hi(float lo, float hi, float c, float s) {
 // Softmax statistics of every 128-column group of the rows of a staged fp32
 // tile (rowstats.h): sf holds tile rows [0, R) at pitch PF, the tile's
 // first row and column are m0 and n0; one thread per (row, group), the
-// group folded in column order from LDS.
+// group's tree over its columns read from LDS.
 template <int R, int BN, int PF, int NT>
 __device__ __forceinline__ void tile_group_stats(float* sf, int m0, int n0, int tid, int Mv,
                                                  int N, const EpiArgs& ea) {
@@ -121,94 +123,11 @@ __device__ __forceinline__ void tile_group_stats(float* sf, int m0, int n0, int 
   }
 }
 
-// acc[i][j][r] holds C[row][col] with row = i*32 + (r/4)*8 + lg*4 + r%4 and
-// col = j*32 + lr inside the wave tile of wave (wm, wn).
-template <int BM, int BN, int EPI, int WM, int WN>
-__device__ __forceinline__ void epilogue_w(f32x16 (&acc)[WM / 32][WN / 32], int m0, int n0, int wm,
-                                           int wn, int lane, int Mv, int N, const EpiArgs& ea) {
-  constexpr int TM = WM / 32, TN = WN / 32;
-  static_assert(EPI != EPI_STORE_F32, "fp32 stores go through a staged epilogue (row statistics)");
-  const int lr = lane & 31, lg = lane >> 5;
-  const int wrow0 = m0 + wm * WM, wcol0 = n0 + wn * WN;
-  if constexpr (EPI == EPI_QKV_ROPE) {
-    const int d = ea.d, dh = ea.dh, T = ea.T, Tp = ea.Tp, H = ea.H, half = dh / 2;
-#pragma unroll
-    for (int j = 0; j < TN; j += 2) {
-      const int col0 = wcol0 + j * 32;  // multiple of 64: a (lo, hi) pair of 32-col blocks
-      const int which = col0 / d, within = col0 % d;
-      const int h = within / dh, jb = (within % dh) / 32;
-#pragma unroll
-      for (int i = 0; i < TM; ++i)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          const int row = wrow0 + i * 32 + (r >> 2) * 8 + lg * 4 + (r & 3);
-          if (row >= Mv) continue;
-          const int b = ea.chunk_of(row), t = row - b * T;
-          const size_t bh = (size_t)b * H + h;
-          const float lo = acc[i][j][r], hi = acc[i][j + 1][r];
-          if (which < 2) {
-            const int dlo = (jb >> 1) * 32 + lr;
-            const float c = ea.rope_cos[t * half + dlo], s = ea.rope_sin[t * half + dlo];
-            bf16_t* dst = (bf16_t*)(which == 0 ? ea.q : ea.k) + (bh * Tp + t) * dh;
-            dst[dlo] = f32_to_bf16(rot_lo(lo, hi, c, s));
-            dst[dlo + half] = f32_to_bf16(rot_hi(lo, hi, c, s));
-          } else {
-            bf16_t* dst = (bf16_t*)ea.vt + bh * dh * Tp + t;
-            const int dim = jb * 32 + lr;
-            dst[(size_t)dim * Tp] = f32_to_bf16(lo);
-            dst[(size_t)(dim + 32) * Tp] = f32_to_bf16(hi);
-          }
-        }
-    }
-  } else if constexpr (EPI == EPI_SWIGLU) {
-#pragma unroll
-    for (int j = 0; j < TN; j += 2) {
-      const int f = (wcol0 + j * 32) / 2 + lr;
-#pragma unroll
-      for (int i = 0; i < TM; ++i)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          const int row = wrow0 + i * 32 + (r >> 2) * 8 + lg * 4 + (r & 3);
-          if (row >= Mv) continue;
-          const float g = acc[i][j][r], u = acc[i][j + 1][r];
-          ((bf16_t*)ea.out)[(size_t)row * ea.ldo + f] = f32_to_bf16(silu(g) * u);
-        }
-    }
-  } else {
-#pragma unroll
-    for (int i = 0; i < TM; ++i)
-#pragma unroll
-      for (int j = 0; j < TN; ++j) {
-        const int col = wcol0 + j * 32 + lr;
-        if (col >= N) continue;
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          const int row = wrow0 + i * 32 + (r >> 2) * 8 + lg * 4 + (r & 3);
-          if (row >= Mv) continue;
-          const size_t o = (size_t)row * ea.ldo + col;
-          if constexpr (EPI == EPI_STORE_F32) {
-            ((float*)ea.out)[o] = acc[i][j][r];
-          } else if constexpr (EPI == EPI_RESIDUAL) {
-            ((float*)ea.out)[o] += acc[i][j][r];
-          } else {
-            ((bf16_t*)ea.out)[o] = f32_to_bf16(gelu_erf(acc[i][j][r]));
-          }
-        }
-      }
-  }
-}
-
-template <int BM, int BN, int EPI>
-__device__ __forceinline__ void epilogue(f32x16 (&acc)[BM / 64][BN / 64], int m0, int n0, int wm,
-                                         int wn, int lane, int Mv, int N, const EpiArgs& ea) {
-  epilogue_w<BM, BN, EPI, BM / 2, BN / 2>(acc, m0, n0, wm, wn, lane, Mv, N, ea);
-}
-
 // ---------------------------------------------------------------------------
-// LDS-staged epilogue.  After the main loop the LDS tile is free: phase 1 has
-// every wave apply its epilogue arithmetic in registers (the same operations,
-// in the same order, as epilogue_w) and park the results in an LDS tile;
-// phase 2 has all threads move 16-byte chunks from LDS to global memory, so
+// LDS-staged epilogue.  acc[i][j][r] of wave (wm, wn) holds C[row][col] with row =
+// i*32 + (r/4)*8 + lg*4 + r%4 and col = j*32 + lr inside the wave's tile.  After
+// the main loop the LDS tile is free: phase 1 has every wave apply its epilogue
+// arithmetic in registers and park the results in an LDS tile; phase 2 has all threads move 16-byte chunks from LDS to global memory, so
 // stores are coalesced -- including V, which the QKV epilogue writes
 // transposed ([dh, Tp] per head).  Rows of an LDS tile carry 8 elements of
 // padding, which puts the two row groups a wave writes at once on different
@@ -703,12 +622,11 @@ gemm_bf16_kernel(const bf16_t* __restrict__ A, const bf16_t* __restrict__ Bw, in
   }
   if constexpr (StagedEpi<BM, BN, EPI>::enabled)
     epilogue_staged<BM, BN, EPI, BM / 2, BN / 2, 256>(acc, smem, m0, n0, wm, wn, tid, Mv, N, ea);
-  else if constexpr ((EPI == EPI_STORE_F32 || EPI == EPI_RESIDUAL) &&
-                     BM / 2 * (BN + 8) * 4 <= StagedEpi<BM, BN, EPI>::smem_elems * 2)
+  else {
     // an fp32 tile too large for the main loop's LDS, staged in two row halves
+    static_assert(BM / 2 * (BN + 8) * 4 <= StagedEpi<BM, BN, EPI>::smem_elems * 2, "a half fits in LDS");
     epilogue_store_halves<EPI, BM, BN, BM / 2, BN / 2, 256>(acc, smem, m0, n0, wm, wn, tid, Mv, N, ea);
-  else
-    epilogue<BM, BN, EPI>(acc, m0, n0, wm, wn, lane, Mv, N, ea);
+  }
 }
 
 // ---------------------------------------------------------------------------
@@ -948,10 +866,10 @@ __device__ __forceinline__ void w4_tile(const bf16_t* __restrict__ A, const bf16
   block_barrier();
   if constexpr (SE::enabled)
     epilogue_staged<BM, BN, EPI, WM, WN, 256>(acc, smem, m0, n0, wm, wn, tid, Mv, N, ea);
-  else if constexpr ((EPI == EPI_STORE_F32 || EPI == EPI_RESIDUAL) && WM * (BN + 8) * 4 <= 160 * 1024)
+  else {
+    static_assert(WM * (BN + 8) * 4 <= 160 * 1024, "a half fits in LDS");
     epilogue_store_halves<EPI, BM, BN, WM, WN, 256>(acc, smem, m0, n0, wm, wn, tid, Mv, N, ea);
-  else
-    epilogue_w<BM, BN, EPI, WM, WN>(acc, m0, n0, wm, wn, lane, Mv, N, ea);
+  }
 }
 
 template <int EPI, int BN, int NSA, int NSB>
@@ -992,11 +910,14 @@ gemm_bf16_w4_split_kernel(const bf16_t* __restrict__ A, const bf16_t* __restrict
 // each wave holds all the MFMA fragments of a k-tile in registers and reads
 // those of the next one under its MFMAs.
 //
-// What bounds it then is the LDS: per k-tile a CU reads the fragments and
-// writes the loads, 48 KB (64 x 64), 72 KB (128 x 64) or 96 KB (128 x 128), and
-// every shape takes 11 cycles per KB of that (0.22, 0.33, 0.46 us per k-tile).
-// So a launch takes the largest tile that still gives every CU one, and tiles
-// that share a CU share its LDS: the time goes by tiles per CU.
+// What a k-tile takes then goes by what a CU moves through its LDS, fragments read
+// and loads written, 48 KB (64 x 64), 72 KB (128 x 64) or 96 KB (128 x 128): 0.22,
+// 0.33, 0.46 us, 11 cycles per KB.  No unit is full at that: at 777 x 4096 x 12288 on
+// 128 x 128 tiles the matrix pipes are busy 43% of the cycles, the LDS' reads 22%,
+// with no bank conflicts, and waves wait 13%; a SIMD has one wave, within which
+// alone its reads, loads and MFMAs overlap.  So a launch takes the largest tile that
+// still gives every CU one, and tiles that share a CU share its LDS: the time goes
+// by tiles per CU.
 //
 // Measured at 1024 rows of the small model (K = 768; FFN-out K = 3072), with
 // the kernels it replaces there: QKV 20.2 -> 10.6 us, O-proj 14.1 -> 5.8, FFN-in
