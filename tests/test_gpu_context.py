@@ -31,3 +31,21 @@ def test_scores_against_the_oracle(dtype, H, dh, Ts):
             tol = 1e-4 if dtype == "f32" else 3e-2
             assert np.max(np.abs(got - ref)) <= tol * np.max(np.abs(ref)) + 1e-6
             assert np.array_equal(got, m.context_scores(toks))
+
+
+@pytest.mark.parametrize("dtype,H,dh", [("f32", 3, 16), ("f32", 1, 128), ("bf16", 2, 64), ("bf16", 1, 128)])
+def test_shorter_chunk_after_a_longer_one(dtype, H, dh):
+    """The buffers of a longer chunk serve a shorter one at its own pitch (an
+    input's last chunk): the same bits as on a fresh model, and as the oracle's."""
+    sh = shape(d_model=H * dh, n_heads=H, d_ffn=128, vocab=300, dtype=dtype, n_layers=2)
+    with dl.Model(sh, max_chunk=700) as used:
+        for T in (700, 300, 65, 64, 17, 1, 333):
+            log("context scores, shorter", dtype, H, dh, T)
+            toks = wl.markov1_tokens(T, sh.vocab, T).astype(np.int32)
+            got = used.context_scores(toks)
+            with dl.Model(sh, max_chunk=T) as fresh:
+                assert np.array_equal(got, fresh.context_scores(toks))
+            if T in (17, 65, 333):
+                ref = OX.context_scores(sh, OW.Weights(sh), toks)
+                tol = 1e-4 if dtype == "f32" else 3e-2
+                assert np.max(np.abs(got - ref)) <= tol * np.max(np.abs(ref)) + 1e-6

@@ -11,13 +11,15 @@ from tests.gpu_common import log, shape
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("H,dh", [(2, 64), (1, 128)])
+@pytest.mark.parametrize("dtype,H,dh", [("bf16", 2, 64), ("bf16", 1, 128), ("f32", 3, 16), ("f32", 4, 32),
+                                        ("f32", 2, 64), ("f32", 1, 128)])
 @pytest.mark.parametrize("T", [1, 33, 95, 129, 389])
-def test_short_chunk_after_long_ones(H, dh, T):
+def test_short_chunk_after_long_ones(dtype, H, dh, T):
     import torch
     # sharpened attention, so that the softmax maxima move between key tiles
-    sh = shape(d_model=128, n_heads=H, d_ffn=128, vocab=300, attn_exp=wl.fan_in_exp(128) - 2)
-    log("stale rows", H, dh, T)
+    d = H * dh
+    sh = shape(d_model=d, n_heads=H, d_ffn=128, vocab=300, dtype=dtype, attn_exp=wl.fan_in_exp(d) - 2)
+    log("stale rows", dtype, H, dh, T)
     dev = torch.from_numpy(wl.random_state(3, 1, T, sh.vocab, 1.0).astype(np.int32)).cuda()
     big = torch.from_numpy(wl.random_state(4, 2, 640, sh.vocab, 0.5).astype(np.int32)).cuda()
     with dl.Model(sh, max_chunk=640, max_batch=2) as m:
