@@ -308,12 +308,12 @@ dlmc_status dlmc_entropy_cdf(dlmc_model* model, const float* logits, int32_t n_r
 /* dlmc_entropy_cdf for callers that cannot allocate device memory (code
  * under HIP graph capture, tight serving loops, harnesses that forbid
  * hipMalloc).  Same arguments and results, bit for bit; no hipMalloc,
- * hipFree or other allocating call: the CDF's per-row tables and segment
- * partials live in the library's static device scratch of DLMC_SCRATCH_BYTES
- * per GPU (held by each GPU the library runs on until the process ends),
- * which must hold 8 n_rows bytes rounded up to 256 plus
- * 20 n_rows ceil(vocab / 4096) bytes when a CDF is asked for (about 6600
- * rows at vocab 126464); larger requests fail with E_INVAL before any work.
+ * hipFree or other allocating call: the CDF's segment partials live in the
+ * library's static device scratch of DLMC_SCRATCH_BYTES per GPU (held by each
+ * GPU the library runs on until the process ends).  When a CDF is asked for,
+ * 8 n_rows bytes rounded up to 256 plus 20 n_rows ceil(vocab / 4096) bytes have
+ * to fit in it (about 6600 rows at vocab 126464); larger requests fail with
+ * E_INVAL before any work.
  * Like dlmc_entropy_cdf it returns once its work on the model's stream is
  * complete.  Every call on a GPU shares that GPU's scratch, so calls that
  * overlap in time on one GPU (other host threads, other model handles)
