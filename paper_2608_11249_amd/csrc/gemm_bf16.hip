@@ -127,9 +127,9 @@ __device__ __forceinline__ void tile_group_stats(float* sf, int m0, int n0, int 
 // LDS-staged epilogue.  acc[i][j][r] of wave (wm, wn) holds C[row][col] with row =
 // i*32 + (r/4)*8 + lg*4 + r%4 and col = j*32 + lr inside the wave's tile.  After
 // the main loop the LDS tile is free: phase 1 has every wave apply its epilogue
-// arithmetic in registers and park the results in an LDS tile; phase 2 has all threads move 16-byte chunks from LDS to global memory, so
-// stores are coalesced -- including V, which the QKV epilogue writes
-// transposed ([dh, Tp] per head).  Rows of an LDS tile carry 8 elements of
+// arithmetic in registers and park the results in an LDS tile; phase 2 has all
+// threads move 16-byte chunks from LDS to global memory, so stores are coalesced
+// -- including V, which the QKV epilogue writes transposed ([dh, Tp] per head).  Rows of an LDS tile carry 8 elements of
 // padding, which puts the two row groups a wave writes at once on different
 // banks.
 // MAIN: LDS bytes of the main loop; BPC: blocks per CU the registers allow
