@@ -46,16 +46,22 @@ void dlmc_model::dfree(void* p) {
 
 void dlmc_model::ensure_sel(int m_max) {
   if (m_max <= sel_cap) return;
-  dfree(sel_pos);
-  dfree(sel_row);
-  dfree(n_sel);
-  dfree(dec);
-  dfree(cdf);
-  dfree(sym);
-  dfree(slot_base);
-  dfree(cdf_ws);
-  dfree(slot_rows);
-  dfree(slot_mx);
+  // nothing of the old buffers is left if an allocation below fails
+  sel_cap = 0;
+  auto drop = [this](auto*& p) {
+    dfree(p);
+    p = nullptr;
+  };
+  drop(sel_pos);
+  drop(sel_row);
+  drop(n_sel);
+  drop(dec);
+  drop(cdf);
+  drop(sym);
+  drop(slot_base);
+  drop(cdf_ws);
+  drop(slot_rows);
+  drop(slot_mx);
   const size_t slots = (size_t)cfg.max_batch * m_max;
   sel_pos = (int32_t*)dalloc(slots * 4, true);
   sel_row = (int32_t*)dalloc(slots * 4, true);
@@ -99,6 +105,8 @@ int32_t* dlmc_model::clear_flag() {
 void dlmc_model::ensure_tokens(size_t n) {
   if (n <= tokens_cap && tokens_dev) return;
   dfree(tokens_dev);
+  tokens_dev = nullptr;
+  tokens_cap = 0;
   tokens_dev = (int32_t*)dalloc(std::max<size_t>(n, 1) * 4);
   tokens_cap = n;
 }

@@ -311,6 +311,9 @@ void dlmc_session::begin_phase() {
 int dlmc_session::step(uint64_t* coded) {
   hipStream_t s = m->stream;
   const int V = m->cfg.vocab, P = cp.cdf_bits, mm = cp.m_max;
+  // the buffers are the model's: a session begun since may have failed to grow them
+  DLMC_CHECK(phase == 2 || (m->sel_cap >= mm && (!encode || m->tokens_cap >= n)), DLMC_E_NOMEM,
+             "the session's buffers were lost when a later session could not allocate its own");
   if (!started) {
     started = true;
     begin_phase();
